@@ -36,6 +36,7 @@
 #include "codec.hpp"
 #include "curvefp_internal.hpp"
 #include "device_util.hpp"
+#include "gemm_small.hpp"
 #include "planes.hpp"
 #include "curvefp_tables.inc"
 
@@ -1379,6 +1380,60 @@ __global__ __launch_bounds__(256) void expand_t_kernel(ExpandTOperand opA, Expan
     }
 }
 
+// fp16 exponent offset of a format's expansion (the row's largest element lands near 2^15)
+int gemm_bias(int f) {
+    constexpr int bias[NUM_FORMATS] = {FmtE4C3::GEMM_BIAS, FmtE5C2::GEMM_BIAS, FmtE3C3::GEMM_BIAS,
+                                       FmtE4C3R89::GEMM_BIAS, FmtE4C3R34::GEMM_BIAS};
+    return bias[f];
+}
+
+// a small product from codes quantized along K (gemm_small.hip), of one or two formats
+hipError_t small_from_codes(const SmallPlan& p, const void* a, const int8_t* as, int fa, const void* b,
+                            const int8_t* bs, int fb, int64_t M, int64_t N, int64_t K, int block, float* c, int64_t ldc,
+                            hipStream_t s) {
+    const Div32 dgq = make_div32((uint32_t)(block / 32));
+    const SmallOperand oa = {a, as, nullptr, M, 0, fa, K / block, dgq}, ob = {b, bs, nullptr, N, 0, fb, K / block, dgq};
+    return launch_gemm_small(p, fa == 2 ? SRC_CODES7 : SRC_CODES8, oa, fb == 2 ? SRC_CODES7 : SRC_CODES8, ob, K, c, ldc,
+                             gemm_bias(fa) + gemm_bias(fb), s);
+}
+
+// and from the planes and row maxima of both operands
+hipError_t small_from_planes(const SmallPlan& p, const char* pa, const int* maxA, const char* pb, const int* maxB,
+                             int64_t M, int64_t N, int64_t K, int64_t rta, int64_t rtb, int bias2, float* c, int64_t ldc,
+                             hipStream_t s) {
+    const SmallOperand oa = {pa, nullptr, maxA, M, rta, 0, 0, Div32{}}, ob = {pb, nullptr, maxB, N, rtb, 0, 0, Div32{}};
+    return launch_gemm_small(p, SRC_PLANES, oa, SRC_PLANES, ob, K, c, ldc, bias2, s);
+}
+
+// the GEMM kernel for the sum of the two operands' offsets: E4C3 and 2^(8/9) 8, E5C2 0, E3C3 12,
+// 2^(3/4) 10, so the sums of any two are 0, 8, 10, 12, 16, 18, 20, 22, 24
+hipError_t launch_gemm_ws_bias(int bias2, dim3 grid, hipStream_t s, const char* pa, const char* pb, const int* maxA,
+                               const int* maxB, int64_t M, int64_t N, int64_t K, int64_t rta, int64_t rtb, float* c,
+                               int64_t ldc, int splits, char* part, int* cnt) {
+    static_assert(FmtE4C3::GEMM_BIAS == 8 && FmtE5C2::GEMM_BIAS == 0 && FmtE3C3::GEMM_BIAS == 12 &&
+                      FmtE4C3R89::GEMM_BIAS == 8 && FmtE4C3R34::GEMM_BIAS == 10,
+                  "the bias sums listed below");
+#define CURVEFP_WS_GEMM(B2)                                                                                     \
+    case B2:                                                                                                  \
+        hipLaunchKernelGGL((gemm_ws_kernel<B2>), grid, dim3(NTHREADS), 0, s, pa, pb, maxA, maxB, M, N, K, rta, \
+                           rtb, c, ldc, splits, part, cnt, ReqOut{});                                         \
+        break;
+    switch (bias2) {
+        CURVEFP_WS_GEMM(0)
+        CURVEFP_WS_GEMM(8)
+        CURVEFP_WS_GEMM(10)
+        CURVEFP_WS_GEMM(12)
+        CURVEFP_WS_GEMM(16)
+        CURVEFP_WS_GEMM(18)
+        CURVEFP_WS_GEMM(20)
+        CURVEFP_WS_GEMM(22)
+        CURVEFP_WS_GEMM(24)
+        default: return hipErrorInvalidValue;
+    }
+#undef CURVEFP_WS_GEMM
+    return hipGetLastError();
+}
+
 template <class F>
 hipError_t launch_ws_fmt(const void* a, const int8_t* as, const void* b, const int8_t* bs, int64_t M,
                          int64_t N, int64_t K, int block, float* c, int64_t ldc, char* ws, int fidx, hipStream_t s) {
@@ -1403,9 +1458,8 @@ hipError_t launch_ws_fmt(const void* a, const int8_t* as, const void* b, const i
     if (e != hipSuccess) return e;
     const int64_t items = w.rta * w.rtb * splits;
     const int64_t grid = (items + 7) / 8 * 8;   // whole XCD shares; surplus workgroups return at once
-    hipLaunchKernelGGL((gemm_ws_kernel<2 * F::GEMM_BIAS>), dim3((unsigned)grid), dim3(NTHREADS), 0, s, ws + w.planes_a,
-                       ws + w.planes_b, maxA, maxB, M, N, K, w.rta, w.rtb, c, ldc, splits, ws + w.part, cnt, ReqOut{});
-    return hipGetLastError();
+    return launch_gemm_ws_bias(2 * F::GEMM_BIAS, dim3((unsigned)grid), s, ws + w.planes_a, ws + w.planes_b, maxA, maxB, M,
+                               N, K, w.rta, w.rtb, c, ldc, splits, ws + w.part, cnt);
 }
 
 // curvefp_gemm_ws with its epilogue requantizing C (see requant_tile): the same prep and
@@ -1442,45 +1496,12 @@ hipError_t launch_requant_fmt(const void* a, const int8_t* as, const void* b, co
     return hipGetLastError();
 }
 
-// fp16 exponent offset of a format's expansion (the row's largest element lands near 2^15)
-int gemm_bias(int f) {
-    constexpr int bias[NUM_FORMATS] = {FmtE4C3::GEMM_BIAS, FmtE5C2::GEMM_BIAS, FmtE3C3::GEMM_BIAS,
-                                       FmtE4C3R89::GEMM_BIAS, FmtE4C3R34::GEMM_BIAS};
-    return bias[f];
-}
-
-// the GEMM kernel for the sum of the two operands' offsets: E4C3 and 2^(8/9) 8, E5C2 0, E3C3 12,
-// 2^(3/4) 10, so the sums of any two are 0, 8, 10, 12, 16, 18, 20, 22, 24
-hipError_t launch_gemm_ws_bias(int bias2, dim3 grid, hipStream_t s, const char* pa, const char* pb, const int* maxA,
-                               const int* maxB, int64_t M, int64_t N, int64_t K, int64_t rta, int64_t rtb, float* c,
-                               int64_t ldc, int splits, char* part, int* cnt) {
-    static_assert(FmtE4C3::GEMM_BIAS == 8 && FmtE5C2::GEMM_BIAS == 0 && FmtE3C3::GEMM_BIAS == 12 &&
-                      FmtE4C3R89::GEMM_BIAS == 8 && FmtE4C3R34::GEMM_BIAS == 10,
-                  "the bias sums listed below");
-#define CURVEFP_WS_GEMM(B2)                                                                                     \
-    case B2:                                                                                                  \
-        hipLaunchKernelGGL((gemm_ws_kernel<B2>), grid, dim3(NTHREADS), 0, s, pa, pb, maxA, maxB, M, N, K, rta, \
-                           rtb, c, ldc, splits, part, cnt, ReqOut{});                                         \
-        break;
-    switch (bias2) {
-        CURVEFP_WS_GEMM(0)
-        CURVEFP_WS_GEMM(8)
-        CURVEFP_WS_GEMM(10)
-        CURVEFP_WS_GEMM(12)
-        CURVEFP_WS_GEMM(16)
-        CURVEFP_WS_GEMM(18)
-        CURVEFP_WS_GEMM(20)
-        CURVEFP_WS_GEMM(22)
-        CURVEFP_WS_GEMM(24)
-        default: return hipErrorInvalidValue;
-    }
-#undef CURVEFP_WS_GEMM
-    return hipGetLastError();
-}
-
 hipError_t launch_mixed(const void* a, const int8_t* as, int fa, int ta, const void* b, const int8_t* bs, int fb,
                         int tb, int64_t M, int64_t N, int64_t K, int block, float* c, int64_t ldc, char* ws,
                         hipStream_t s) {
+    SmallPlan sp;
+    const bool small = small_plan(M, N, K, &sp);
+    if (small && !ta && !tb) return small_from_codes(sp, a, as, fa, b, bs, fb, M, N, K, block, c, ldc, s);
     const MixedLayout x = mixed_layout(M, N, K);
     const WsLayout& w = x.w;
     const int64_t nkb = K / 32;
@@ -1547,6 +1568,9 @@ hipError_t launch_mixed(const void* a, const int8_t* as, int fa, int ta, const v
         if (e == hipSuccess) e = tb ? expand_t(xb, xn, p7b) : expand_k(kbo, kn, p7b);
     }
     if (e != hipSuccess) return e;
+    if (small)
+        return small_from_planes(sp, ws + w.planes_a, maxA, ws + w.planes_b, maxB, M, N, K, w.rta, w.rtb,
+                                 gemm_bias(fa) + gemm_bias(fb), c, ldc, s);
     const int64_t items = tiles * splits;
     const dim3 grid((unsigned)((items + 7) / 8 * 8));
     return launch_gemm_ws_bias(gemm_bias(fa) + gemm_bias(fb), grid, s, ws + w.planes_a, ws + w.planes_b, maxA, maxB,
@@ -1696,6 +1720,11 @@ hipError_t launch_gemm_prepared(const void* pa, int fa, const void* pb, int fb, 
     const PreparedGemmLayout g = prepared_gemm_layout(M, N, K);
     const char* a = reinterpret_cast<const char*>(pa);
     const char* b = reinterpret_cast<const char*>(pb);
+    SmallPlan sp;
+    if (small_plan(M, N, K, &sp))
+        return small_from_planes(sp, a + la.planes, reinterpret_cast<const int*>(a + la.rmax), b + lb.planes,
+                                 reinterpret_cast<const int*>(b + lb.rmax), M, N, K, la.rt, lb.rt,
+                                 gemm_bias(fa) + gemm_bias(fb), c, ldc, s);
     const int64_t tiles = la.rt * lb.rt;
     char* w = reinterpret_cast<char*>(ws);
     int* cnt = g.splits > 1 ? reinterpret_cast<int*>(w + g.cnt) : nullptr;
@@ -1720,6 +1749,14 @@ hipError_t launch_gemm_requant(const void* a, const int8_t* as, const void* b, c
                                int8_t* out_scales, void* ws, hipStream_t s) {
     char* w = reinterpret_cast<char*>(ws);
     uint8_t* qc = reinterpret_cast<uint8_t*>(out_codes);
+    SmallPlan sp;
+    if (small_plan(M, N, K, &sp)) {
+        // C goes to the workspace (it fits: small_plan) and is quantized from there
+        float* c = reinterpret_cast<float*>(ws);
+        const hipError_t e = small_from_codes(sp, a, as, format, b, bs, format, M, N, K, block, c, N, s);
+        if (e != hipSuccess) return e;
+        return launch_quantize(c, 0, M, N, N, 1, out_format, out_block, out_codes, out_scales, s);
+    }
     switch (format) {
         case 0: return launch_requant_fmt<FmtE4C3>(a, as, b, bs, M, N, K, block, w, 0, out_format, out_block, qc, out_scales, s);
         case 1: return launch_requant_fmt<FmtE5C2>(a, as, b, bs, M, N, K, block, w, 1, out_format, out_block, qc, out_scales, s);
@@ -1738,6 +1775,8 @@ hipError_t launch_gemm_mixed(const void* a, const int8_t* as, int fa, int ta, co
 hipError_t launch_gemm_ws(const void* a, const int8_t* as, const void* b, const int8_t* bs, int64_t M,
                           int64_t N, int64_t K, int format, int block, float* c, int64_t ldc, void* ws,
                           hipStream_t s) {
+    SmallPlan sp;
+    if (small_plan(M, N, K, &sp)) return small_from_codes(sp, a, as, format, b, bs, format, M, N, K, block, c, ldc, s);
     char* w = reinterpret_cast<char*>(ws);
     switch (format) {
         case 0: return launch_ws_fmt<FmtE4C3>(a, as, b, bs, M, N, K, block, c, ldc, w, 0, s);
@@ -1751,6 +1790,8 @@ hipError_t launch_gemm_ws(const void* a, const int8_t* as, const void* b, const 
 
 hipError_t launch_gemm(const void* a, const int8_t* as, const void* b, const int8_t* bs, int64_t M,
                        int64_t N, int64_t K, int format, int block, float* c, int64_t ldc, hipStream_t s) {
+    SmallPlan sp;
+    if (small_plan(M, N, K, &sp)) return small_from_codes(sp, a, as, format, b, bs, format, M, N, K, block, c, ldc, s);
     switch (format) {
         case 0: return launch_fmt<FmtE4C3>(a, as, b, bs, M, N, K, block, c, ldc, 0, s);
         case 1: return launch_fmt<FmtE5C2>(a, as, b, bs, M, N, K, block, c, ldc, 1, s);
