@@ -36,6 +36,7 @@
 #include "codec.hpp"
 #include "curvefp_internal.hpp"
 #include "device_util.hpp"
+#include "gemm_mid.hpp"
 #include "gemm_small.hpp"
 #include "planes.hpp"
 #include "curvefp_tables.inc"
@@ -1405,11 +1406,28 @@ hipError_t small_from_planes(const SmallPlan& p, const char* pa, const int* maxA
     return launch_gemm_small(p, SRC_PLANES, oa, SRC_PLANES, ob, K, c, ldc, bias2, s);
 }
 
+// Whether the 128 x 128 tiles of gemm_mid.hip are faster than the 256 x 256 ones (same C bit for bit).
+// A round of either keeps the 256 compute units busy once; a round of 128 x 128 tiles holds half the work
+// and takes about 0.6 of the time (4096 K: 95 against 161 us with every unit busy, 65 against 107 us with
+// a quarter of them), so it pays where the larger tiles leave more of their rounds empty: 512 x 4096
+// x 4096 66 against 107 us, 1300 x 6144 x 2048 (3 rounds against 2) 131 against 153 us, but
+// 1500 x 4096 x 4096 (2 against 1) 160 against 143 us.  From 256 large tiles on K is not split and the
+// larger tiles always win.
+bool mid_tiles(int64_t M, int64_t N, int64_t K) {
+    const WsLayout w = ws_layout(M, N, K);
+    const int64_t large = w.rta * w.rtb * w.splits, small = ((M + 127) / 128) * ((N + 127) / 128);
+    if (w.rta * w.rtb >= 256) return false;
+    const int64_t per_round = w.splits == 2 ? 256 : 512;   // unsplit, two workgroups share a unit
+    return 6 * ((small + per_round - 1) / per_round) < 10 * ((large + 255) / 256);
+}
+
 // the GEMM kernel for the sum of the two operands' offsets: E4C3 and 2^(8/9) 8, E5C2 0, E3C3 12,
 // 2^(3/4) 10, so the sums of any two are 0, 8, 10, 12, 16, 18, 20, 22, 24
 hipError_t launch_gemm_ws_bias(int bias2, dim3 grid, hipStream_t s, const char* pa, const char* pb, const int* maxA,
                                const int* maxB, int64_t M, int64_t N, int64_t K, int64_t rta, int64_t rtb, float* c,
                                int64_t ldc, int splits, char* part, int* cnt) {
+    if (mid_tiles(M, N, K))
+        return launch_gemm_mid(pa, pb, maxA, maxB, M, N, K, rta, rtb, c, ldc, bias2, splits, s);
     static_assert(FmtE4C3::GEMM_BIAS == 8 && FmtE5C2::GEMM_BIAS == 0 && FmtE3C3::GEMM_BIAS == 12 &&
                       FmtE4C3R89::GEMM_BIAS == 8 && FmtE4C3R34::GEMM_BIAS == 10,
                   "the bias sums listed below");
@@ -1728,7 +1746,7 @@ hipError_t launch_gemm_prepared(const void* pa, int fa, const void* pb, int fb, 
     const int64_t tiles = la.rt * lb.rt;
     char* w = reinterpret_cast<char*>(ws);
     int* cnt = g.splits > 1 ? reinterpret_cast<int*>(w + g.cnt) : nullptr;
-    if (g.splits > 1) {
+    if (g.splits > 1 && !mid_tiles(M, N, K)) {
         // prep_kernel with no operands: its one extra workgroup clears the arrival counters
         hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(256), 0, s, (const int8_t*)nullptr, (const int8_t*)nullptr,
                            (int64_t)0, (int64_t)0, (int64_t)0, 0, 0, (int*)nullptr, (int*)nullptr, cnt, (int)tiles);
