@@ -102,10 +102,19 @@ def _fmt(fmt) -> int:
     return FORMATS[fmt] if isinstance(fmt, str) else int(fmt)
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+# The stream handle of a call is an integer (a hipStream_t).  Asking for the current stream's handle
+# alone takes 0.1 us where torch.cuda.current_stream() takes 2.7 us for the Stream object around it, of
+# the 11 us a call took on the host in all.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _check(st: int, what: str):
@@ -147,19 +156,17 @@ def _device_error(what, tensors, stream):
 
 def _on_gpu(what: str, tensors, stream=None):
     """All tensors on one GPU, the current device (and the stream's, when one is given)."""
-    idx = None
+    idx = -1
     for _, t in tensors:
-        if not isinstance(t, torch.Tensor) or not t.is_cuda:
-            if isinstance(t, torch.Tensor) and t.device.type in _GPU_DEVICE_TYPES:
+        d = t.get_device() if isinstance(t, torch.Tensor) and t.is_cuda else -1
+        if d != idx or d < 0:
+            if d >= 0 and idx < 0:
+                idx = d
+            elif isinstance(t, torch.Tensor) and not t.is_cuda and t.device.type in _GPU_DEVICE_TYPES:
                 continue             # a device the tests of these checks admit (no GPU index)
-            return _device_error(what, tensors, stream)
-        d = t.get_device()
-        if idx is None:
-            idx = d
-        elif d != idx:
-            return _device_error(what, tensors, stream)
-    if idx is not None and (idx != torch.cuda.current_device()
-                            or (stream is not None and getattr(stream, "device_index", idx) != idx)):
+            else:
+                return _device_error(what, tensors, stream)
+    if idx >= 0 and (idx != _device() or (stream is not None and getattr(stream, "device_index", idx) != idx)):
         return _device_error(what, tensors, stream)
 
 
@@ -205,6 +212,9 @@ def _scales_arg(what, name, t, outer, k, block):
 
 def _source_arg(what, src):
     """A 2-D fp32 or bf16 source (its row stride is the library's ld_src)."""
+    st = src.stride()
+    if len(st) == 2 and st[1] == 1 and src.dtype in DTYPES and (st[0] >= src.shape[1] or src.shape[0] <= 1):
+        return
     if src.dim() != 2:
         raise ValueError(f"{what}: src must be 2-D, got {src.dim()} dimensions")
     _matrix(what, "src", src, src.shape[0], src.shape[1], tuple(DTYPES))
@@ -248,7 +258,12 @@ def curvefp_quantize(src: torch.Tensor, fmt, block_axis: int = 1, block: int = 3
     block: elements per scale, a multiple of 32 dividing the blocked extent.
     """
     what = "curvefp_quantize"
-    _on_gpu(what, [("src", src)], stream)
+    ts = [("src", src)]
+    if codes is not None:
+        ts.append(("codes", codes))
+    if scales is not None:
+        ts.append(("scales", scales))
+    _on_gpu(what, ts, stream)
     _source_arg(what, src)
     rows, cols = src.shape
     outer, k = (rows, cols) if block_axis == 1 else (cols, rows)
@@ -260,7 +275,6 @@ def curvefp_quantize(src: torch.Tensor, fmt, block_axis: int = 1, block: int = 3
         assert codes.numel() == nbytes
     if scales is None:
         scales = torch.empty((outer, k // block), dtype=torch.int8, device=src.device)
-    _on_gpu(what, [("src", src), ("codes", codes), ("scales", scales)], stream)
     _codes_arg(what, "codes", codes, f, outer, k, block)
     _scales_arg(what, "scales", scales, outer, k, block)
     st = lib().curvefp_quantize(src.data_ptr(), DTYPES[src.dtype], rows, cols, src.stride(0),
@@ -275,7 +289,12 @@ def curvefp_quantize_mse(src: torch.Tensor, fmt, block_axis: int = 1, candidates
                          stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """curvefp_quantize with static-operand scales chosen by reconstruction-MSE search."""
     what = "curvefp_quantize_mse"
-    _on_gpu(what, [("src", src)], stream)
+    ts = [("src", src)]
+    if codes is not None:
+        ts.append(("codes", codes))
+    if scales is not None:
+        ts.append(("scales", scales))
+    _on_gpu(what, ts, stream)
     _source_arg(what, src)
     rows, cols = src.shape
     outer, k = (rows, cols) if block_axis == 1 else (cols, rows)
@@ -285,7 +304,6 @@ def curvefp_quantize_mse(src: torch.Tensor, fmt, block_axis: int = 1, candidates
         codes = torch.empty(shape, dtype=torch.uint8, device=src.device)
     if scales is None:
         scales = torch.empty((outer, k // block), dtype=torch.int8, device=src.device)
-    _on_gpu(what, [("src", src), ("codes", codes), ("scales", scales)], stream)
     _codes_arg(what, "codes", codes, f, outer, k, block)
     _scales_arg(what, "scales", scales, outer, k, block)
     st = lib().curvefp_quantize_mse(src.data_ptr(), DTYPES[src.dtype], rows, cols, src.stride(0), block_axis, f,
@@ -385,10 +403,10 @@ def curvefp_dequantize(codes: torch.Tensor, scales: torch.Tensor, fmt, outer: in
                        stream=None) -> torch.Tensor:
     what = "curvefp_dequantize"
     f = _fmt(fmt)
-    _on_gpu(what, [("codes", codes), ("scales", scales)], stream)
+    ts = [("codes", codes), ("scales", scales)]
+    _on_gpu(what, ts if dst is None else ts + [("dst", dst)], stream)
     if dst is None:
         dst = torch.empty((outer, k), dtype=torch.float32, device=codes.device)
-    _on_gpu(what, [("codes", codes), ("scales", scales), ("dst", dst)], stream)
     _codes_arg(what, "codes", codes, f, outer, k, block)
     _scales_arg(what, "scales", scales, outer, k, block)
     _matrix(what, "dst", dst, outer, k, (torch.float32,))
@@ -398,11 +416,15 @@ def curvefp_dequantize(codes: torch.Tensor, scales: torch.Tensor, fmt, outer: in
     return dst
 
 
-def _gemm_args(what, a_codes, a_scales, b_codes, b_scales, M, N, K, f, block, c, stream):
+def _gemm_args(what, a_codes, a_scales, b_codes, b_scales, M, N, K, f, block, c, stream, workspace=None):
     """Operands of a single-format GEMM: A codes/scales of an [M, K] tensor, B of an [N, K]
     tensor, blocks along K; c (if given) at least M x N fp32."""
     ts = [("a_codes", a_codes), ("a_scales", a_scales), ("b_codes", b_codes), ("b_scales", b_scales)]
-    _on_gpu(what, ts + ([("c", c)] if c is not None else []), stream)
+    if c is not None:
+        ts.append(("c", c))
+    if workspace is not None:
+        ts.append(("workspace", workspace))
+    _on_gpu(what, ts, stream)
     _codes_arg(what, "a_codes", a_codes, f, M, K, block)
     _scales_arg(what, "a_scales", a_scales, M, K, block)
     _codes_arg(what, "b_codes", b_codes, f, N, K, block)
@@ -445,13 +467,13 @@ def curvefp_gemm_ws(a_codes: torch.Tensor, a_scales: torch.Tensor, b_codes: torc
                     stream=None) -> torch.Tensor:
     """The product of curvefp_gemm, through a workspace (codes expanded once)."""
     what = "curvefp_gemm_ws"
-    _on_gpu(what, [("a_codes", a_codes)], stream)
+    if c is None or workspace is None:
+        _on_gpu(what, [("a_codes", a_codes)], stream)
     if c is None:
         c = torch.empty((M, N), dtype=torch.float32, device=a_codes.device)
     if workspace is None:
         workspace = gemm_workspace(M, N, K, a_codes.device)
-    _gemm_args(what, a_codes, a_scales, b_codes, b_scales, M, N, K, _fmt(fmt), block, c, stream)
-    _on_gpu(what, [("a_codes", a_codes), ("workspace", workspace)], stream)
+    _gemm_args(what, a_codes, a_scales, b_codes, b_scales, M, N, K, _fmt(fmt), block, c, stream, workspace)
     _dense(what, "workspace", workspace, curvefp_gemm_workspace_bytes(M, N, K))
     st = lib().curvefp_gemm_ws(a_codes.data_ptr(), a_scales.data_ptr(), b_codes.data_ptr(),
                                b_scales.data_ptr(), M, N, K, _fmt(fmt), block, c.data_ptr(), c.stride(0),
