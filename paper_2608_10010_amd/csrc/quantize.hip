@@ -20,6 +20,7 @@
 #include "curvefp_internal.hpp"
 #include "device_util.hpp"
 #include "planes.hpp"
+#include "quantize_rules.hpp"
 #include "curvefp_tables.inc"
 
 #include <cstring>
@@ -41,93 +42,6 @@ __constant__ uint64_t g_qr_sig[NUM_FORMATS][128] = CURVEFP_QR_SIG_INIT;
 __constant__ uint32_t g_qp_dec[NUM_FORMATS][GEMM_DEC_ENTRIES] = CURVEFP_DEC_INIT;
 
 namespace {
-
-template <class F>
-__device__ __forceinline__ int block_scale(uint32_t amax, uint32_t lmax_mant) {
-    // an all-zero block (every integer a satisfies 0 <= 2^a fl32(L_max)) and a subnormal maximum
-    // both take the bottom of the scale range
-    const int ef = (int)(amax >> 23);
-    if (ef == 0) return -127;
-    const int a = ef - 127 - F::OHI + (((amax & 0x7FFFFFu) > lmax_mant) ? 1 : 0);
-    return min(max(a, -127), 127);
-}
-
-// rank of y whose fp32 bit pattern is yb (already scaled), table in LDS
-template <class F>
-__device__ __forceinline__ uint32_t rank_lookup(int32_t yb, const uint32_t* lut) {
-    int32_t idx = (yb >> 16) - ((127 + F::OZ) << 7);
-    if (idx < 0) return 0;
-    idx = min(idx, F::QLUT_SIZE - 1);
-    const uint32_t e = lut[idx];
-    return (e >> 16) + ((((uint32_t)yb & 0xFFFFu) > (e & 0xFFFFu)) ? 1u : 0u);
-}
-
-// the same for a yb whose low 16 bits are zero, with the one-byte table
-template <class F>
-__device__ __forceinline__ uint32_t rank_lookup(int32_t yb, const uint8_t* lut) {
-    int32_t idx = (yb >> 16) - ((127 + F::OZ) << 7);
-    if (idx < 0) return 0;
-    return lut[min(idx, F::QLUT_SIZE - 1)];
-}
-
-// fast path: a >= A_FAST_MIN, where subnormal or zero inputs can only reach rank 0
-template <class F, class T>
-__device__ __forceinline__ uint32_t rank_fast(uint32_t mag, int a, const T* lut) {
-    return rank_lookup<F>((int32_t)mag - (a << 23), lut);
-}
-
-// exact path for blocks with tiny scales: normalize subnormal inputs first
-template <class F, class T>
-__device__ __forceinline__ uint32_t rank_exact(uint32_t mag, int a, const T* lut) {
-    if (mag == 0) return 0;
-    int32_t yb;
-    if ((mag >> 23) == 0) {
-        const int p = 31 - __clz(mag);              // position of the leading one, 0..22
-        const uint32_t mn = mag << (23 - p);
-        yb = (int32_t)(((uint32_t)(p - 22 - a) << 23) | (mn & 0x7FFFFFu));
-    } else {
-        yb = (int32_t)mag - (a << 23);
-    }
-    return rank_lookup<F>(yb, lut);
-}
-
-template <class F, class T>
-__device__ __forceinline__ void ranks_of(const uint32_t* mag, int n, int a, const T* lut, uint32_t* r) {
-    if (a == -128) {
-        for (int i = 0; i < n; i++) r[i] = 0;
-    } else if (a >= F::A_FAST_MIN) {
-        for (int i = 0; i < n; i++) r[i] = rank_fast<F>(mag[i], a, lut);
-    } else {
-        for (int i = 0; i < n; i++) r[i] = rank_exact<F>(mag[i], a, lut);
-    }
-}
-
-template <class F>
-__device__ __forceinline__ int scale_of(uint32_t amax, uint32_t lmax_mant) {
-    return (amax >= 0x7F800000u) ? -128 : block_scale<F>(amax, lmax_mant);
-}
-
-// unpack 8 consecutive source elements into magnitude bits (as fp32) and sign bits
-template <bool BF16>
-__device__ __forceinline__ void unpack8(const uint4* v, uint32_t* mag, uint32_t* sgn) {
-    if (BF16) {
-        const uint32_t w[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            mag[2 * i] = (w[i] << 16) & 0x7FFF0000u;
-            mag[2 * i + 1] = w[i] & 0x7FFF0000u;
-            sgn[2 * i] = (w[i] >> 15) & 1u;
-            sgn[2 * i + 1] = w[i] >> 31;
-        }
-    } else {
-        const uint32_t w[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            mag[i] = w[i] & 0x7FFFFFFFu;
-            sgn[i] = w[i] >> 31;
-        }
-    }
-}
 
 // the maximum over the 2^lgl lanes (lgl in 2..6, aligned groups, all active) that hold one
 // block: DPP within 16 lanes (after the quad maximum, a half-row mirror pairs each lane with
@@ -892,366 +806,6 @@ hipError_t launch_compact_fmt(const void* src, int dtype, int64_t rows, int64_t 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Static-operand scales (Sec. 3.1: weights quantized once pick, among representable powers of two,
-// the scale that minimizes the squared reconstruction error).  One thread per block (of 32 here; larger blocks below): the block is quantized at each
-// candidate scale a_c + u (a_c ceil-absmax; u = 0, -1, .., -(candidates - 1), then 1 .. P - 1
-// when the level pattern spans P > 1 octaves), each element reconstructed to fp32 exactly as the
-// dequantizer does, and the squared error summed in fp64 in index order; the first candidate
-// with the least error wins.  Offline work for weights, run once per tensor.
-
-// fp32 bits -> the same value in fp64, exactly, without the fp32 denormal mode's say
-__device__ __forceinline__ double f64_of_f32_bits(uint32_t b) {
-    const uint32_t e = (b >> 23) & 0xFFu, m = b & 0x7FFFFFu;
-    double v;
-    if (e == 0) {
-        v = (double)m * 0x1p-149;                    // exact: m < 2^23, a power-of-two scale
-    } else {
-        const uint64_t d = ((uint64_t)(e - 127 + 1023) << 52) | ((uint64_t)m << 29);
-        v = __builtin_bit_cast(double, d);
-    }
-    return (b >> 31) ? -v : v;
-}
-
-// acc + d * d as two roundings (no fused multiply-add), so the sum is the same everywhere
-__device__ __forceinline__ double add_square(double acc, double d) {
-#pragma clang fp contract(off)
-    const double sq = d * d;
-    return acc + sq;
-}
-
-// rank of one magnitude at scale a (the fast or the exact path of ranks_of)
-template <class F>
-__device__ __forceinline__ uint32_t rank_at(uint32_t mag, int a, const uint32_t* lut) {
-    return a >= F::A_FAST_MIN ? rank_fast<F>(mag, a, lut) : rank_exact<F>(mag, a, lut);
-}
-
-// squared reconstruction error of one element at scale a, added to acc (fp64, index order)
-template <class F>
-__device__ __forceinline__ double add_element_error(double acc, uint32_t m, uint32_t s, double x, int a,
-                                                    const uint32_t* lut, const uint32_t* mant, const uint64_t* sig) {
-    const uint32_t rk = rank_at<F>(m, a, lut);
-    const uint32_t code = rk | ((rk != 0 ? s : 0u) << F::EC);
-    const double xh = f64_of_f32_bits(value_bits<F>(code, a, mant, sig));
-    return add_square(acc, x - xh);
-}
-
-// candidates per block at most: 8 below or at the ceil-absmax scale, P - 1 <= 2 above it
-constexpr int MSE_MAXC = 10;
-
-// One thread per block.  The block's magnitudes sit in LDS ([element][thread], so a wave's
-// reads of one element are conflict-free); one pass over the 32 elements updates every
-// candidate's error sum, each in index order, so each element is converted once and only the
-// sums stay in registers (the candidate loop is unrolled and guarded by the wave-uniform count).
-template <class F, bool BF16>
-__global__ __launch_bounds__(256) void quantize_mse_kernel(
-    const void* __restrict__ src, int64_t rows, int64_t cols, int64_t ld, int axis, int candidates,
-    uint8_t* __restrict__ codes, int8_t* __restrict__ scales, int fidx) {
-    __shared__ uint32_t lut[F::QLUT_SIZE];
-    constexpr int RT = F::BINARY ? 8 : 128;
-    __shared__ uint32_t mant[RT];
-    __shared__ uint64_t sig[RT];
-    __shared__ uint32_t smag[32 * 256];
-    for (int i = threadIdx.x; i < F::QLUT_SIZE; i += blockDim.x) lut[i] = g_qlut[fidx][i];
-    if (threadIdx.x < RT) {
-        mant[threadIdx.x] = g_qr_mant[fidx][threadIdx.x];
-        sig[threadIdx.x] = g_qr_sig[fidx][threadIdx.x];
-    }
-    const uint32_t lmax_mant = g_lmax_mant[fidx];
-    __syncthreads();
-    // block b: axis 1 -> row b / (cols / 32), block b mod (cols / 32) of it; axis 0 -> column
-    // b mod cols, rows 32 (b / cols) ..: consecutive threads take consecutive columns
-    const int64_t nbr = axis == 1 ? cols / 32 : rows / 32;          // blocks per output row
-    const int64_t nb = axis == 1 ? rows * nbr : cols * nbr;
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= nb) return;
-    uint32_t* my = smag + threadIdx.x;                              // element i at my[256 i]
-    int64_t orow, oblk;                                             // output row and block in it
-    uint32_t sgn = 0, amax = 0;
-    if (axis == 1) {
-        orow = b / nbr;
-        oblk = b - orow * nbr;
-        if (BF16) {
-            const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(src) + orow * ld + 32 * oblk);
-#pragma unroll
-            for (int t = 0; t < 4; t++) {
-                const uint4 v = p[t];
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const uint32_t m0 = (w[j] << 16) & 0x7FFF0000u, m1 = w[j] & 0x7FFF0000u;
-                    my[256 * (8 * t + 2 * j)] = m0;
-                    my[256 * (8 * t + 2 * j + 1)] = m1;
-                    amax = max(amax, max(m0, m1));
-                    sgn |= ((w[j] >> 15) & 1u) << (8 * t + 2 * j);
-                    sgn |= (w[j] >> 31) << (8 * t + 2 * j + 1);
-                }
-            }
-        } else {
-            const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(src) + orow * ld + 32 * oblk);
-#pragma unroll
-            for (int t = 0; t < 8; t++) {
-                const uint4 v = p[t];
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const uint32_t m = w[j] & 0x7FFFFFFFu;
-                    my[256 * (4 * t + j)] = m;
-                    amax = max(amax, m);
-                    sgn |= (w[j] >> 31) << (4 * t + j);
-                }
-            }
-        }
-    } else {
-        const int64_t rb = b / cols;
-        orow = b - rb * cols;                                       // the source column
-        oblk = rb;
-#pragma unroll
-        for (int i = 0; i < 32; i++) {
-            const int64_t e = (32 * rb + i) * ld + orow;
-            const uint32_t w = BF16 ? ((uint32_t)reinterpret_cast<const uint16_t*>(src)[e] << 16)
-                                    : reinterpret_cast<const uint32_t*>(src)[e];
-            my[256 * i] = w & 0x7FFFFFFFu;
-            amax = max(amax, w & 0x7FFFFFFFu);
-            sgn |= (w >> 31) << i;
-        }
-    }
-    const int ac = scale_of<F>(amax, lmax_mant);
-    const bool live = ac != -128 && amax != 0;
-    int best_a = ac;
-    if (live) {
-        const int nc = candidates + F::PERIOD - 1;
-        int acand[MSE_MAXC];
-        bool ok[MSE_MAXC];
-        double acc[MSE_MAXC];
-#pragma unroll
-        for (int c = 0; c < MSE_MAXC; c++) {
-            acand[c] = c < candidates ? ac - c : ac + (c - candidates + 1);
-            ok[c] = c < nc && acand[c] >= -127 && acand[c] <= 127;
-            acc[c] = 0.0;
-        }
-#pragma unroll 2
-        for (int i = 0; i < 32; i++) {
-            const uint32_t m = my[256 * i];
-            const uint32_t s = (sgn >> i) & 1u;
-            const double x = f64_of_f32_bits(m | (s << 31));
-#pragma unroll
-            for (int c = 0; c < MSE_MAXC; c++)
-                if (c < nc && ok[c]) acc[c] = add_element_error<F>(acc[c], m, s, x, acand[c], lut, mant, sig);
-        }
-        // the first candidate in the order above with the least error
-        double best_err = acc[0];
-#pragma unroll
-        for (int c = 1; c < MSE_MAXC; c++)
-            if (c < nc && ok[c] && acc[c] < best_err) {
-                best_err = acc[c];
-                best_a = acand[c];
-            }
-    }
-    uint32_t cc[32];
-#pragma unroll
-    for (int i = 0; i < 32; i++) {
-        const uint32_t rk = live ? rank_at<F>(my[256 * i], best_a, lut) : 0u;
-        cc[i] = rk | ((rk != 0 ? (sgn >> i) & 1u : 0u) << F::EC);
-    }
-    if (!F::PACKED7) {
-        uint4* o = reinterpret_cast<uint4*>(codes + (orow * nbr + oblk) * 32);
-#pragma unroll
-        for (int q = 0; q < 2; q++) {
-            uint32_t k[4];
-#pragma unroll
-            for (int j = 0; j < 4; j++)
-                k[j] = cc[16 * q + 4 * j] | (cc[16 * q + 4 * j + 1] << 8) | (cc[16 * q + 4 * j + 2] << 16) |
-                       (cc[16 * q + 4 * j + 3] << 24);
-            o[q] = make_uint4(k[0], k[1], k[2], k[3]);
-        }
-    } else {
-        uint32_t wds[7] = {0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < 32; i++) {
-            const int bit = 7 * i;
-            wds[bit >> 5] |= cc[i] << (bit & 31);
-            if ((bit & 31) > 25) wds[(bit >> 5) + 1] |= cc[i] >> (32 - (bit & 31));
-        }
-        uint32_t* o = reinterpret_cast<uint32_t*>(codes + (orow * nbr + oblk) * 28);
-#pragma unroll
-        for (int j = 0; j < 7; j++) o[j] = wds[j];
-    }
-    scales[orow * nbr + oblk] = (int8_t)best_a;
-}
-
-// The same search for blocks of G > 32 elements (Sec. 4.2's PTQ weights use G64 and G512): one
-// thread per block streams it from memory three times (its maximum; every candidate's error
-// sum, element by element in index order; the codes at the winning scale, 32 at a time), so
-// only the candidates' sums stay in registers.  Blocks along rows are read 8 elements per
-// 16-byte load; blocks down the columns one element per load (consecutive threads take
-// consecutive columns).
-template <class F, bool BF16>
-__device__ __forceinline__ void mse_load8(const void* __restrict__ src, int axis, int64_t base, int64_t ld, int j,
-                                          uint32_t* mag, uint32_t& sgn8) {
-    sgn8 = 0;
-    if (axis == 1) {
-        const char* p = reinterpret_cast<const char*>(src) + (base + 8 * (int64_t)j) * (BF16 ? 2 : 4);
-        uint4 v[BF16 ? 1 : 2];
-#pragma unroll
-        for (int t = 0; t < (BF16 ? 1 : 2); t++) v[t] = ld16<false>(reinterpret_cast<const uint4*>(p) + t);
-        uint32_t sg[8];
-        unpack8<BF16>(v, mag, sg);
-#pragma unroll
-        for (int e = 0; e < 8; e++) sgn8 |= sg[e] << e;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int64_t idx = base + (8 * (int64_t)j + e) * ld;
-            const uint32_t w = BF16 ? ((uint32_t)reinterpret_cast<const uint16_t*>(src)[idx] << 16)
-                                    : reinterpret_cast<const uint32_t*>(src)[idx];
-            mag[e] = w & 0x7FFFFFFFu;
-            sgn8 |= (w >> 31) << e;
-        }
-    }
-}
-
-template <class F, bool BF16>
-__global__ __launch_bounds__(256) void quantize_mse_g_kernel(
-    const void* __restrict__ src, int64_t rows, int64_t cols, int64_t ld, int axis, int G, int candidates,
-    uint8_t* __restrict__ codes, int8_t* __restrict__ scales, int fidx) {
-    __shared__ uint32_t lut[F::QLUT_SIZE];
-    constexpr int RT = F::BINARY ? 8 : 128;
-    __shared__ uint32_t mant[RT];
-    __shared__ uint64_t sig[RT];
-    for (int i = threadIdx.x; i < F::QLUT_SIZE; i += blockDim.x) lut[i] = g_qlut[fidx][i];
-    if (threadIdx.x < RT) {
-        mant[threadIdx.x] = g_qr_mant[fidx][threadIdx.x];
-        sig[threadIdx.x] = g_qr_sig[fidx][threadIdx.x];
-    }
-    const uint32_t lmax_mant = g_lmax_mant[fidx];
-    __syncthreads();
-    const int64_t k = axis == 1 ? cols : rows;                   // blocked extent
-    const int64_t nbr = k / G;                                    // blocks per output row
-    const int64_t nb = axis == 1 ? rows * nbr : cols * nbr;
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= nb) return;
-    int64_t orow, oblk, base;                                     // output row, block, first element
-    if (axis == 1) {
-        orow = b / nbr;
-        oblk = b - orow * nbr;
-        base = orow * ld + oblk * G;
-    } else {
-        oblk = b / cols;
-        orow = b - oblk * cols;                                   // the source column
-        base = oblk * G * ld + orow;
-    }
-    const int nch = G / 8;
-    uint32_t amax = 0;
-    for (int j = 0; j < nch; j++) {
-        uint32_t mag[8], sg;
-        mse_load8<F, BF16>(src, axis, base, ld, j, mag, sg);
-#pragma unroll
-        for (int e = 0; e < 8; e++) amax = max(amax, mag[e]);
-    }
-    const int ac = scale_of<F>(amax, lmax_mant);
-    const bool live = ac != -128 && amax != 0;
-    int best_a = ac;
-    if (live) {
-        const int nc = candidates + F::PERIOD - 1;
-        int acand[MSE_MAXC];
-        bool ok[MSE_MAXC];
-        double acc[MSE_MAXC];
-#pragma unroll
-        for (int c = 0; c < MSE_MAXC; c++) {
-            acand[c] = c < candidates ? ac - c : ac + (c - candidates + 1);
-            ok[c] = c < nc && acand[c] >= -127 && acand[c] <= 127;
-            acc[c] = 0.0;
-        }
-        for (int j = 0; j < nch; j++) {
-            uint32_t mag[8], sg;
-            mse_load8<F, BF16>(src, axis, base, ld, j, mag, sg);
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const uint32_t s = (sg >> e) & 1u;
-                const double x = f64_of_f32_bits(mag[e] | (s << 31));
-#pragma unroll
-                for (int c = 0; c < MSE_MAXC; c++)
-                    if (c < nc && ok[c])
-                        acc[c] = add_element_error<F>(acc[c], mag[e], s, x, acand[c], lut, mant, sig);
-            }
-        }
-        double best_err = acc[0];
-#pragma unroll
-        for (int c = 1; c < MSE_MAXC; c++)
-            if (c < nc && ok[c] && acc[c] < best_err) {
-                best_err = acc[c];
-                best_a = acand[c];
-            }
-    }
-    // codes, one group of 32 at a time
-    for (int grp = 0; grp < G / 32; grp++) {
-        uint32_t cc[32];
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            uint32_t mag[8], sg;
-            mse_load8<F, BF16>(src, axis, base, ld, 4 * grp + q, mag, sg);
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const uint32_t rk = live ? rank_at<F>(mag[e], best_a, lut) : 0u;
-                cc[8 * q + e] = rk | ((rk != 0 ? (sg >> e) & 1u : 0u) << F::EC);
-            }
-        }
-        const int64_t g32 = orow * (k / 32) + oblk * (G / 32) + grp;   // group of 32 in the output
-        if (!F::PACKED7) {
-            uint4* o = reinterpret_cast<uint4*>(codes + g32 * 32);
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                uint32_t w4[4];
-#pragma unroll
-                for (int t = 0; t < 4; t++)
-                    w4[t] = cc[16 * h + 4 * t] | (cc[16 * h + 4 * t + 1] << 8) | (cc[16 * h + 4 * t + 2] << 16) |
-                            (cc[16 * h + 4 * t + 3] << 24);
-                o[h] = make_uint4(w4[0], w4[1], w4[2], w4[3]);
-            }
-        } else {
-            uint32_t wds[7] = {0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int i = 0; i < 32; i++) {
-                const int bit = 7 * i;
-                wds[bit >> 5] |= cc[i] << (bit & 31);
-                if ((bit & 31) > 25) wds[(bit >> 5) + 1] |= cc[i] >> (32 - (bit & 31));
-            }
-            uint32_t* o = reinterpret_cast<uint32_t*>(codes + g32 * 28);
-#pragma unroll
-            for (int t = 0; t < 7; t++) o[t] = wds[t];
-        }
-    }
-    scales[orow * nbr + oblk] = (int8_t)best_a;
-}
-
-template <class F>
-hipError_t launch_mse_fmt(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, int axis,
-                          int block, int candidates, int fidx, void* codes, int8_t* scales, hipStream_t s) {
-    uint8_t* cp = reinterpret_cast<uint8_t*>(codes);
-    if (block > 32) {
-        const int64_t nbg = rows * cols / block;
-        const dim3 gg((unsigned)((nbg + 255) / 256));
-        if (dtype == 1)
-            hipLaunchKernelGGL((quantize_mse_g_kernel<F, true>), gg, dim3(256), 0, s, src, rows, cols, ld, axis, block,
-                               candidates, cp, scales, fidx);
-        else
-            hipLaunchKernelGGL((quantize_mse_g_kernel<F, false>), gg, dim3(256), 0, s, src, rows, cols, ld, axis, block,
-                               candidates, cp, scales, fidx);
-        return hipGetLastError();
-    }
-    const int64_t nb = rows * cols / 32;
-    const dim3 grid((unsigned)((nb + 255) / 256));
-    if (dtype == 1)
-        hipLaunchKernelGGL((quantize_mse_kernel<F, true>), grid, dim3(256), 0, s, src, rows, cols, ld, axis, candidates,
-                           cp, scales, fidx);
-    else
-        hipLaunchKernelGGL((quantize_mse_kernel<F, false>), grid, dim3(256), 0, s, src, rows, cols, ld, axis, candidates,
-                           cp, scales, fidx);
-    return hipGetLastError();
-}
-
-
-// ---------------------------------------------------------------------------------------------
 // Quantize and prepare in one launch: Q(X) of Sec. 3.1 with blocks along the rows, then the
 // result's staging as a GEMM operand (Sec. 3.3) -- the planes and row maxima that curvefp_prepare
 // writes from these codes (planes.hpp) -- and, when dst is given, the reconstruction of
@@ -1563,17 +1117,6 @@ hipError_t launch_quantize_prepare_pair(const void* src_a, int64_t rows_a, int64
     return qp_launch(qp_operand(src_a, rows_a, k, ld_a, codes_a, scales_a, prepared_a, dst_a, ld_dst_a),
                      qp_operand(src_b, rows_b, k, ld_b, codes_b, scales_b, prepared_b, dst_b, ld_dst_b), dtype, k,
                      format, block, s);
-}
-
-hipError_t launch_quantize_mse(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, int axis,
-                               int format, int block, int candidates, void* codes, int8_t* scales, hipStream_t s) {
-    switch (format) {
-        case 0: return launch_mse_fmt<FmtE4C3>(src, dtype, rows, cols, ld, axis, block, candidates, 0, codes, scales, s);
-        case 1: return launch_mse_fmt<FmtE5C2>(src, dtype, rows, cols, ld, axis, block, candidates, 1, codes, scales, s);
-        case 2: return launch_mse_fmt<FmtE3C3>(src, dtype, rows, cols, ld, axis, block, candidates, 2, codes, scales, s);
-        case 3: return launch_mse_fmt<FmtE4C3R89>(src, dtype, rows, cols, ld, axis, block, candidates, 3, codes, scales, s);
-        default: return launch_mse_fmt<FmtE4C3R34>(src, dtype, rows, cols, ld, axis, block, candidates, 4, codes, scales, s);
-    }
 }
 
 hipError_t launch_quantize_compact(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, int format,
