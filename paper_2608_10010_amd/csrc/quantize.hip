@@ -322,7 +322,11 @@ __global__ __launch_bounds__(256) void block_scales_cols_kernel(const void* __re
     }
 }
 
-template <class F, bool BF16, int U>
+// NT: streaming loads.  fp32 sources: at most 4096 workgroups, each looping, and plain loads (the table is
+// twice to four times bfloat16's, so more and shorter workgroups spend their time filling it: 4000 x 11008 to
+// E5C2 58.7 us with up to 32768 workgroups, 46.8 with 4096; 8192 x 14336 147 and 113 us).  bfloat16: up to
+// 32768 (4096 measured 2-9% faster on E5C2, 4% slower on 32768 x 8192 and on E3C3).
+template <class F, bool BF16, int U, bool NT = BF16>
 hipError_t launch_rows_u(const void* src, int64_t rows, int64_t cols, int64_t ld, int fidx, uint8_t* codes,
                          int8_t* scales, int block, int lgl, Div32 dgl, hipStream_t s) {
     const int64_t cpr = cols / 8;
@@ -332,11 +336,12 @@ hipError_t launch_rows_u(const void* src, int64_t rows, int64_t cols, int64_t ld
         const int64_t nr = rows - r0 < slab ? rows - r0 : slab;
         const int64_t nchunks = nr * cpr;
         int64_t blocks = (nchunks + 256 * U - 1) / (256 * U);
-        blocks = blocks < 32768 ? blocks : 32768;
+        constexpr int64_t MOST = BF16 ? 32768 : 4096;
+        blocks = blocks < MOST ? blocks : MOST;
         const void* sp = reinterpret_cast<const char*>(src) + r0 * ld * (BF16 ? 2 : 4);
         uint8_t* cp = codes + (F::PACKED7 ? r0 * (cols / 32) * 28 : r0 * cols);
         int8_t* scp = scales + r0 * (cols / block);
-        hipLaunchKernelGGL((quantize_rows_kernel<F, BF16, U, true, true>), dim3(blocks), dim3(256), 0, s, sp,
+        hipLaunchKernelGGL((quantize_rows_kernel<F, BF16, U, NT, true>), dim3(blocks), dim3(256), 0, s, sp,
                            (uint32_t)nchunks, (uint32_t)cpr, make_div32((uint32_t)cpr), ld, cp, scp, fidx, lgl, dgl);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -770,24 +775,26 @@ __global__ __launch_bounds__(256) void scales_unpack_kernel(const int8_t* __rest
     scales[i] = (int8_t)(d == (1 << S) - 1 ? -128 : (int)row_ref[r] - d);
 }
 
-// Tensorwise scales: one ceil-absmax scale for the whole tensor.  A 4-byte workspace word is
-// cleared, every workgroup folds the largest magnitude bits it reads into it (atomicMax on the
-// fp32 bit pattern: non-negative floats order as integers, NaN above infinity), the scale is
-// written once per output row (the rowwise layout, all entries equal), and the quantize kernels
-// then read it as the scale of a block spanning the whole blocked extent.
-__global__ void tensor_max_clear_kernel(uint32_t* __restrict__ word) { *word = 0u; }
+// Tensorwise scales: one ceil-absmax scale for the whole tensor.  The workgroups of the first pass leave
+// their maxima (fp32 bit patterns: non-negative floats order as integers, NaN above infinity) at the start of
+// the code buffer, which holds nothing yet; the second pass reduces them and writes the scale once per output
+// row (the rowwise layout, all entries equal); the quantize kernels then read it as the scale of a block
+// spanning the whole blocked extent, and overwrite the maxima with codes.  (Folding the maxima into one word
+// took a launch to clear it and one atomic per workgroup on the same address, which serialize: no more than
+// 256 workgroups could share the read.  4096 x 4096 bf16: 34 us in four launches, 21.5 in three.)
+constexpr int TENSOR_MAX_GROUPS = 1024;
 
 // VEC: rows 16-byte aligned with cols % 8 == 0, read in chunks of 8 elements (n = rows * cols / 8
 // chunks, row of chunk g = g / (cols / 8)); otherwise one element at a time (n = rows * cols).
 // n < 2^32 either way (the launcher checks).
-template <bool BF16, bool VEC>
+// NT: streaming loads, for tensors too large to stay in the 256 MB cache until they are quantized
+template <bool BF16, bool VEC, bool NT>
 __global__ __launch_bounds__(256) void tensor_max_kernel(const void* __restrict__ src, uint32_t n, uint32_t per_row,
-                                                         Div32 dpr, int64_t ld, uint32_t* __restrict__ word) {
+                                                         Div32 dpr, int64_t ld, uint32_t* __restrict__ part) {
     constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int NV = BF16 ? 1 : 2;
     uint32_t m = 0;
-    // four units in flight per thread: the grid is small (every workgroup ends in one atomic on
-    // the same word, and those serialize), so each thread streams many units
+    // four units in flight per thread
 #pragma unroll 4
     for (uint32_t g = blockIdx.x * 256u + threadIdx.x; g < n; g += gridDim.x * 256u) {
         const uint32_t r = div32(g, dpr), c = g - r * per_row;
@@ -796,7 +803,7 @@ __global__ __launch_bounds__(256) void tensor_max_kernel(const void* __restrict_
                                                             ((int64_t)r * ld + 8 * (int64_t)c) * ESZ);
             uint4 v[NV];
 #pragma unroll
-            for (int t = 0; t < NV; t++) v[t] = ld16<true>(p + t);
+            for (int t = 0; t < NV; t++) v[t] = ld16<NT>(p + t);
             uint32_t mag[8], sgn[8];
             unpack8<BF16>(v, mag, sgn);
 #pragma unroll
@@ -813,22 +820,36 @@ __global__ __launch_bounds__(256) void tensor_max_kernel(const void* __restrict_
     __shared__ uint32_t wm[4];
     if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) atomicMax(word, max(max(wm[0], wm[1]), max(wm[2], wm[3])));
+    if (threadIdx.x == 0) part[blockIdx.x] = max(max(wm[0], wm[1]), max(wm[2], wm[3]));
 }
 
 template <class F>
-__global__ __launch_bounds__(256) void tensor_scale_kernel(const uint32_t* __restrict__ word, int64_t outer,
-                                                           int8_t* __restrict__ scales, int fidx) {
-    const int a = scale_of<F>(*word, g_lmax_mant[fidx]);
+__global__ __launch_bounds__(256) void tensor_scale_kernel(const uint32_t* __restrict__ part, int64_t nparts,
+                                                           int64_t outer, int8_t* __restrict__ scales, int fidx) {
+    uint32_t m = 0;
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < nparts; i += 256) m = max(m, part[i]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    __shared__ uint32_t wm[4];
+    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+    __syncthreads();
+    const int a = scale_of<F>(max(max(wm[0], wm[1]), max(wm[2], wm[3])), g_lmax_mant[fidx]);
     for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < outer; r += (int64_t)gridDim.x * 256)
         scales[r] = (int8_t)a;
 }
 
 template <class F>
 hipError_t launch_tensorwise_fmt(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, int axis,
-                                 int fidx, void* codes, int8_t* scales, uint32_t* word, hipStream_t s) {
-    hipLaunchKernelGGL(tensor_max_clear_kernel, dim3(1), dim3(1), 0, s, word);
+                                 int fidx, void* codes, int8_t* scales, hipStream_t s) {
+    // a group of 256 threads takes at least 1024 units of eight codes (one, unaligned): its word in the code
+    // buffer is always there
+    uint32_t* part = reinterpret_cast<uint32_t*>(codes);
+    int64_t nparts = 0;
     const int64_t esz0 = dtype == 1 ? 2 : 4;
+    // plain loads keep a source of up to half the 256 MB cache there for the second read (1511 x 5152 bf16
+    // 14.3 -> 12.0 us); larger ones stream (14368 x 13056 bf16: 181 us, 196 with plain loads)
+    const bool large = rows * cols * esz0 > ((int64_t)128 << 20);
     const bool vec = cols % 8 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0 && (ld * esz0) % 16 == 0;
     const int64_t per_row = vec ? cols / 8 : cols;
     // slabs of rows keep the unit count of one launch at most 2^32 - 2^21, so the grid-stride
@@ -837,26 +858,30 @@ hipError_t launch_tensorwise_fmt(const void* src, int dtype, int64_t rows, int64
     for (int64_t r0 = 0; r0 < rows; r0 += slab) {
         const int64_t nr = rows - r0 < slab ? rows - r0 : slab;
         const uint32_t n = (uint32_t)(nr * per_row);
-        int64_t g = ((int64_t)n + 255) / 256;
-        g = g < 256 ? g : 256;                 // one workgroup per compute unit, 256 atomics
+        int64_t g = ((int64_t)n + 1023) / 1024;
+        g = g < TENSOR_MAX_GROUPS ? g : TENSOR_MAX_GROUPS;
+        uint32_t* word = part + nparts;
+        nparts += g;
         const void* sp = reinterpret_cast<const char*>(src) + r0 * ld * esz0;
         const Div32 dpr = make_div32((uint32_t)per_row);
+#define CURVEFP_TENSOR_MAX(B, V, NT)                                                                                \
+    hipLaunchKernelGGL((tensor_max_kernel<B, V, NT>), dim3((unsigned)g), dim3(256), 0, s, sp, n, (uint32_t)per_row, \
+                       dpr, ld, word)
         if (dtype == 1) {
-            if (vec) hipLaunchKernelGGL((tensor_max_kernel<true, true>), dim3((unsigned)g), dim3(256), 0, s, sp, n,
-                                        (uint32_t)per_row, dpr, ld, word);
-            else hipLaunchKernelGGL((tensor_max_kernel<true, false>), dim3((unsigned)g), dim3(256), 0, s, sp, n,
-                                    (uint32_t)per_row, dpr, ld, word);
+            if (!vec) CURVEFP_TENSOR_MAX(true, false, false);
+            else if (large) CURVEFP_TENSOR_MAX(true, true, true);
+            else CURVEFP_TENSOR_MAX(true, true, false);
         } else {
-            if (vec) hipLaunchKernelGGL((tensor_max_kernel<false, true>), dim3((unsigned)g), dim3(256), 0, s, sp, n,
-                                        (uint32_t)per_row, dpr, ld, word);
-            else hipLaunchKernelGGL((tensor_max_kernel<false, false>), dim3((unsigned)g), dim3(256), 0, s, sp, n,
-                                    (uint32_t)per_row, dpr, ld, word);
+            if (!vec) CURVEFP_TENSOR_MAX(false, false, false);
+            else if (large) CURVEFP_TENSOR_MAX(false, true, true);
+            else CURVEFP_TENSOR_MAX(false, true, false);
         }
+#undef CURVEFP_TENSOR_MAX
     }
     const int64_t outer = axis == 1 ? rows : cols;
     int64_t gs = (outer + 255) / 256;
-    gs = gs < 1024 ? gs : 1024;
-    hipLaunchKernelGGL((tensor_scale_kernel<F>), dim3((unsigned)gs), dim3(256), 0, s, word, outer, scales, fidx);
+    gs = gs < 256 ? gs : 256;   // each reads all the maxima
+    hipLaunchKernelGGL((tensor_scale_kernel<F>), dim3((unsigned)gs), dim3(256), 0, s, part, nparts, outer, scales, fidx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the quantize pass with the scale given, one block per output row of the blocked extent
@@ -865,8 +890,10 @@ hipError_t launch_tensorwise_fmt(const void* src, int dtype, int64_t rows, int64
     if (axis == 1) {
         const Div32 dgl = make_div32((uint32_t)(cols / 8));
         const int64_t nchunks = rows * (cols / 8);
-        if (dtype == 1)   // bf16: two chunks per thread at every size, as curvefp_quantize
+        if (dtype == 1 && large)   // bf16: two chunks per thread at every size, as curvefp_quantize
             return launch_rows_u<F, true, 2>(src, rows, cols, ld, fidx, cp, scales, (int)cols, -1, dgl, s);
+        if (dtype == 1)
+            return launch_rows_u<F, true, 2, false>(src, rows, cols, ld, fidx, cp, scales, (int)cols, -1, dgl, s);
         if (nchunks >= (int64_t)2048 * 256 * 2)
             return launch_rows_u<F, false, 2>(src, rows, cols, ld, fidx, cp, scales, (int)cols, -1, dgl, s);
         return launch_rows_u<F, false, 1>(src, rows, cols, ld, fidx, cp, scales, (int)cols, -1, dgl, s);
@@ -1258,13 +1285,13 @@ hipError_t launch_scales_unpack(const int8_t* row_ref, const uint8_t* offsets, i
 
 hipError_t launch_quantize_tensorwise(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, int axis,
                                      int format, void* codes, int8_t* scales, void* workspace, hipStream_t s) {
-    uint32_t* w = reinterpret_cast<uint32_t*>(workspace);
+    (void)workspace;   // the entry point still asks for its word; the maxima now pass through the code buffer
     switch (format) {
-        case 0: return launch_tensorwise_fmt<FmtE4C3>(src, dtype, rows, cols, ld, axis, 0, codes, scales, w, s);
-        case 1: return launch_tensorwise_fmt<FmtE5C2>(src, dtype, rows, cols, ld, axis, 1, codes, scales, w, s);
-        case 2: return launch_tensorwise_fmt<FmtE3C3>(src, dtype, rows, cols, ld, axis, 2, codes, scales, w, s);
-        case 3: return launch_tensorwise_fmt<FmtE4C3R89>(src, dtype, rows, cols, ld, axis, 3, codes, scales, w, s);
-        default: return launch_tensorwise_fmt<FmtE4C3R34>(src, dtype, rows, cols, ld, axis, 4, codes, scales, w, s);
+        case 0: return launch_tensorwise_fmt<FmtE4C3>(src, dtype, rows, cols, ld, axis, 0, codes, scales, s);
+        case 1: return launch_tensorwise_fmt<FmtE5C2>(src, dtype, rows, cols, ld, axis, 1, codes, scales, s);
+        case 2: return launch_tensorwise_fmt<FmtE3C3>(src, dtype, rows, cols, ld, axis, 2, codes, scales, s);
+        case 3: return launch_tensorwise_fmt<FmtE4C3R89>(src, dtype, rows, cols, ld, axis, 3, codes, scales, s);
+        default: return launch_tensorwise_fmt<FmtE4C3R34>(src, dtype, rows, cols, ld, axis, 4, codes, scales, s);
     }
 }
 
