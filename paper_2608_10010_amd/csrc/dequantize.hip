@@ -25,132 +25,122 @@ __constant__ uint64_t g_dq_sig62[NUM_FORMATS][128] = CURVEFP_DQ_SIG62_INIT;
 
 namespace {
 
-// chunk g = 8 consecutive codes: chunk g mod cpr of row g / cpr, block g / 4 (blocks are
-// contiguous in the code and scale arrays); a grid-stride loop over the chunks, one per thread
-// per round (a capped grid with plain stores measured fastest for this write-heavy stream; the
-// cap grows with the tensor, see the launch), or with TWO, two rounds per pass whose loads are
-// all issued before the first chunk is written
-template <class F, bool TWO>
-__global__ __launch_bounds__(256) void dequantize_kernel(
-    const uint8_t* __restrict__ codes, const int8_t* __restrict__ scales, uint32_t nchunks, uint32_t cpr,
-    Div32 dcpr, int64_t ld, float* __restrict__ dst, int fidx, Div32 dgq) {
+// Four consecutive codes (a quad) and 16 bytes of fp32 per lane and step, so that every store of a wave is one
+// contiguous kilobyte and can stream past the caches (eight codes per lane wrote 32 bytes in two halves, each
+// store with holes, which wants the caches to merge them); U quads per lane, 256 apart, are requested before
+// the first is written.  A level's bits at a scale that keeps it a normal number are its bits at scale 0 plus
+// the scale in the exponent field: one table lookup and one add; other scales take value_bits.
+// HBM-bound: 4000 x 11008 E4C3 51.0 -> 33.1 us (220 MB, 6.7 TB/s: the largest cache takes part), 32768 x 8192
+// 275 -> 234 us (5.8 TB/s), 2048 x 4096 E3C3 13.0 -> 8.2 us, 16 x 4096 3.2 -> 2.7 us.
+template <class F, int U>
+__global__ __launch_bounds__(256) void dequantize_kernel(const uint8_t* __restrict__ codes,
+                                                         const int8_t* __restrict__ scales, uint64_t nquads,
+                                                         uint32_t qpr, bool dense, Div32 dqpr, int64_t ld, float* __restrict__ dst,
+                                                         int fidx, Div32 dgq) {
     constexpr int TAB = F::BINARY ? 8 : 128;
     __shared__ uint32_t mant[TAB];
     __shared__ uint64_t sig[TAB];
-    if (threadIdx.x < TAB) {
-        mant[threadIdx.x] = F::BINARY ? g_mant[fidx][threadIdx.x] : g_dq_em[fidx][threadIdx.x];
-        sig[threadIdx.x] = F::BINARY ? g_sig62[fidx][threadIdx.x] : g_dq_sig62[fidx][threadIdx.x];
+    __shared__ uint32_t val0[F::NMAG];
+    uint32_t w[U];
+    int a[U];
+    auto fetch = [&](uint64_t q0) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint64_t q = q0 + 256u * u;
+            if (q >= nquads) break;
+            const uint32_t b = (uint32_t)(q >> 3);   // group of 32; its scale is that of block b / (G / 32)
+            a[u] = scales[div32(b, dgq)];
+            if (!F::PACKED7) {
+                w[u] = *reinterpret_cast<const uint32_t*>(codes + q * 4);
+            } else {
+                // bits [28 j, 28 j + 28) of the group's 28 bytes: the four bytes from 7 j / 2 hold them
+                const uint32_t j = (uint32_t)q & 7u;
+                uint32_t x;
+                __builtin_memcpy(&x, codes + (uint64_t)b * 28 + ((7 * j) >> 1), 4);
+                w[u] = (j & 1) ? x >> 4 : x;
+            }
+        }
+    };
+    const uint64_t q0 = (uint64_t)blockIdx.x * (256u * U) + threadIdx.x;
+    fetch(q0);
+    const int t = (int)threadIdx.x;
+    if (t < TAB) {
+        mant[t] = F::BINARY ? g_mant[fidx][t] : g_dq_em[fidx][t];
+        sig[t] = F::BINARY ? g_sig62[fidx][t] : g_dq_sig62[fidx][t];
+    }
+    if (t < F::NMAG) {
+        uint32_t v = 0;
+        if (t > 0) {
+            const int n = t - F::B;
+            const uint32_t em = F::BINARY ? 0u : g_dq_em[fidx][t & 127];
+            v = F::BINARY ? ((uint32_t)((n >> F::C) + 127) << 23) | g_mant[fidx][n & (F::K - 1) & 7]
+                          : ((uint32_t)(((int32_t)em >> 24) + 127) << 23) | (em & 0x7FFFFFu);
+        }
+        val0[t] = v;
     }
     __syncthreads();
-    const bool dense = ld == (int64_t)cpr * 8;
-    const uint32_t stride = gridDim.x * 256u;
-    // the words of chunk g (8 codes) and its block's scale
-    auto fetch = [&](uint32_t g, uint2& w, uint32_t& w2, int& a) {
-        const uint32_t b = g >> 2;                  // 32-element group; its scale is that of block b / (G / 32)
-        a = scales[div32(b, dgq)];
-        if (!F::PACKED7) {
-            w = *reinterpret_cast<const uint2*>(codes + (uint64_t)g * 8);
-            w2 = 0u;
-        } else {
-            // bytes [7 part, 7 part + 7) of the block's 28 bytes; parts 1 and 2 (bytes 7..13 and
-            // 14..20) straddle three dwords, parts 0 and 3 two
-            const uint32_t* base = reinterpret_cast<const uint32_t*>(codes + (uint64_t)b * 28);
-            const int part = (int)(g & 3);
-            const int d0 = (7 * part) >> 2;
-            w = make_uint2(base[d0], base[d0 + 1]);
-            w2 = (part == 1 || part == 2) ? base[d0 + 2] : 0u;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const uint64_t q = q0 + 256u * u;
+        if (q >= nquads) break;
+        int64_t e = (int64_t)q * 4;
+        if (!dense) {
+            const uint32_t r = div32((uint32_t)q, dqpr);
+            e = (int64_t)r * ld + (int64_t)((uint32_t)q - r * qpr) * 4;
         }
-    };
-    auto emit = [&](uint32_t g, uint2 w, uint32_t w2, int a) {
-        uint32_t c[8];
-        if (!F::PACKED7) {
+        constexpr int CB = F::PACKED7 ? 7 : 8;
+        // every level is a normal number at these scales (octaves OZ + 1 .. OHI)
+        if (a[u] >= -127 - F::OZ && a[u] <= 127 - F::OHI) {
+            const uint32_t a23 = (uint32_t)a[u] << 23;
+            uint32_t o[4];
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                c[i] = (w.x >> (8 * i)) & 0xFFu;
-                c[4 + i] = (w.y >> (8 * i)) & 0xFFu;
+                const uint32_t c = (w[u] >> (CB * i)) & ((1u << CB) - 1);
+                const uint32_t m = c & F::MAG_MASK;
+                o[i] = m != 0 ? (val0[m] + a23) | ((c >> F::EC) << 31) : 0u;
             }
+            st16<true>(dst + e, o[0], o[1], o[2], o[3]);
         } else {
-            const int part = (int)(g & 3);
-            const int off = 7 * part - 4 * ((7 * part) >> 2);
-            const uint64_t lo = (uint64_t)w.x | ((uint64_t)w.y << 32);
-            const uint64_t hi = w2;
-            const uint64_t chunk = off ? ((lo >> (8 * off)) | (hi << (64 - 8 * off))) : lo;
-#pragma unroll
-            for (int i = 0; i < 8; i++) c[i] = (uint32_t)(chunk >> (7 * i)) & 0x7Fu;
+            // rare: element by element, so that the common path keeps its registers
+            uint32_t x = w[u];
+#pragma unroll 1
+            for (int i = 0; i < 4; i++, x >>= CB)
+                dst[e + i] = __builtin_bit_cast(float, a[u] == -128 ? 0x7FC00000u   // poisoned block
+                                                                    : value_bits<F>(x & ((1u << CB) - 1), a[u],
+                                                                                    mant, sig));
         }
-        uint32_t o[8];
-        if (a == -128) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) o[i] = 0x7FC00000u;   // poisoned block
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; i++) o[i] = value_bits<F>(c[i], a, mant, sig);
-        }
-        int64_t e;
-        if (dense) {
-            e = (int64_t)g * 8;
-        } else {
-            const uint32_t r = div32(g, dcpr);
-            e = (int64_t)r * ld + (int64_t)(g - r * cpr) * 8;
-        }
-        uint4* out = reinterpret_cast<uint4*>(dst + e);
-        out[0] = make_uint4(o[0], o[1], o[2], o[3]);
-        out[1] = make_uint4(o[4], o[5], o[6], o[7]);
-    };
-    if (!TWO) {
-        for (uint32_t g = blockIdx.x * 256u + threadIdx.x; g < nchunks; g += stride) {
-            uint2 w;
-            uint32_t x;
-            int a;
-            fetch(g, w, x, a);
-            emit(g, w, x, a);
-        }
-        return;
     }
-    // large grids: two chunks per thread and pass (g and g + stride), both requested before either
-    // is written (64-bit positions: g + 2 stride can pass 2^32)
-    for (uint64_t p = (uint64_t)blockIdx.x * 256u + threadIdx.x; p < nchunks; p += 2ull * stride) {
-        const uint32_t g0 = (uint32_t)p;
-        const bool two = p + stride < nchunks;
-        const uint32_t g1 = two ? (uint32_t)(p + stride) : g0;
-        uint2 w0, w1 = make_uint2(0u, 0u);
-        uint32_t x0, x1 = 0u;
-        int a0, a1 = 0;
-        fetch(g0, w0, x0, a0);
-        if (two) fetch(g1, w1, x1, a1);
-        emit(g0, w0, x0, a0);
-        if (two) emit(g1, w1, x1, a1);
-    }
+}
+
+template <class F, int U>
+void launch_quads(const uint8_t* codes, const int8_t* scales, int64_t rows, int64_t qpr, float* dst, int64_t ld,
+                  int fidx, Div32 dgq, hipStream_t s) {
+    const int64_t nquads = rows * qpr, blocks = (nquads + 256 * U - 1) / (256 * U);
+    // rows without gaps (a single row among them) need no row index, which is 32 bits wide
+    const bool dense = rows == 1 || ld == 4 * qpr;
+    const uint32_t q = dense ? 1u : (uint32_t)qpr;
+    hipLaunchKernelGGL((dequantize_kernel<F, U>), dim3((unsigned)blocks), dim3(256), 0, s, codes, scales,
+                       (uint64_t)nquads, q, dense, make_div32(q), ld, dst, fidx, dgq);
 }
 
 template <class F>
 hipError_t launch_fmt(const void* codes, const int8_t* scales, int64_t outer, int64_t k, int block, float* dst,
                       int64_t ld, int fidx, hipStream_t s) {
     const Div32 dgq = make_div32((uint32_t)(block / 32));
-    const int64_t cpr = k / 8;
-    const int64_t slab = ((int64_t)1 << 31) / cpr;   // 32-bit chunk indices per launch
+    const int64_t qpr = k / 4;
+    // 32-bit quad indices per launch where rows are told apart (two rows or more)
+    const int64_t slab = qpr < ((int64_t)1 << 31) ? ((int64_t)1 << 31) / qpr : 1;
     const uint8_t* cp = reinterpret_cast<const uint8_t*>(codes);
     for (int64_t r0 = 0; r0 < outer; r0 += slab) {
         const int64_t nr = outer - r0 < slab ? outer - r0 : slab;
-        const int64_t nchunks = nr * cpr;
-        // two chunks per thread (two rounds) once that takes more than 8192 workgroups, else at
-        // most 8192: on 8192 x 4096 codes more workgroups measured slower, on 32768 x 8192 the
-        // 8192 cap 13% slower than two rounds
-        const int64_t half = (nchunks + 511) / 512;
-        int64_t blocks = (nchunks + 255) / 256;
-        const int64_t cap = half > 8192 ? half : 8192;
-        blocks = blocks < cap ? blocks : cap;
-        // the two rounds of large grids with both chunks' loads in flight at once (16% faster on
-        // 32768 x 8192 from HBM; on grids of at most 8192 workgroups the plain loop measured faster)
         const uint8_t* cr = cp + (F::PACKED7 ? r0 * (k / 32) * 28 : r0 * k);
-        if (half > 8192)
-            hipLaunchKernelGGL((dequantize_kernel<F, true>), dim3((unsigned)blocks), dim3(256), 0, s, cr,
-                               scales + r0 * (k / block), (uint32_t)nchunks, (uint32_t)cpr,
-                               make_div32((uint32_t)cpr), ld, dst + r0 * ld, fidx, dgq);
+        const int8_t* sr = scales + r0 * (k / block);
+        // two quads per lane (one and four are within 5% up to 64 M elements), eight from there on, where the
+        // output no longer fits the 256 MB cache: 32768 x 8192 E3C3 267 us with two, 230 with eight
+        if (nr * qpr >= (int64_t)1 << 24)
+            launch_quads<F, 8>(cr, sr, nr, qpr, dst + r0 * ld, ld, fidx, dgq, s);
         else
-            hipLaunchKernelGGL((dequantize_kernel<F, false>), dim3((unsigned)blocks), dim3(256), 0, s, cr,
-                               scales + r0 * (k / block), (uint32_t)nchunks, (uint32_t)cpr,
-                               make_div32((uint32_t)cpr), ld, dst + r0 * ld, fidx, dgq);
+            launch_quads<F, 2>(cr, sr, nr, qpr, dst + r0 * ld, ld, fidx, dgq, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
