@@ -1157,12 +1157,20 @@ hipError_t launch_qp_u(const QPOperand& a, const QPOperand& b, int64_t k, int fi
     return hipGetLastError();
 }
 
+// With few rows (at most QP_FEW_TILES tiles of 256, the padding included) rows of 129 to 512 chunks take
+// a workgroup each as well: a wave per row leaves most of the chip idle and gives each wave up to 8 chunks
+// per lane to work through.  Measured, one bf16 operand: 32 x 4096 10.8 -> 5.6 us, 256 x 2048 7.2 -> 4.9,
+// 1024 x 4096 13.2 -> 10.1; 4096 x 4096 would go from 23.4 to 31.8, and rows of 128 chunks (1000 x 1024)
+// from 5.7 to 6.2, so those keep a wave per row.
+constexpr int64_t QP_FEW_TILES = 4;
+
 // Rows of up to 512 chunks (bf16; 256 fp32: 2, 4 or 8 chunks per lane) take one wave each,
 // rows of up to 1024 bf16 (512 fp32) chunks one workgroup each, staged in at most 32 KB of LDS
 // per workgroup; qp_fused_rows decides which rows go here at all.
 template <class F, bool BF16>
 hipError_t launch_qp(const QPOperand& a, const QPOperand& b, int64_t k, int fidx, int block, hipStream_t s) {
     const int64_t cpr = k / 8;
+    if (a.RT + b.RT <= QP_FEW_TILES && cpr > 128 && cpr <= 512) return launch_qp_u<F, BF16, 2, 4>(a, b, k, fidx, block, s);
     if (cpr <= 128) return launch_qp_u<F, BF16, 2, 1>(a, b, k, fidx, block, s);
     if (cpr <= 256) return launch_qp_u<F, BF16, 4, 1>(a, b, k, fidx, block, s);
     if constexpr (BF16) {
