@@ -796,8 +796,9 @@ __device__ __forceinline__ WorkItem work_item(int tiles_y, int tiles_x, int spli
 // requantization to a finite destination may saturate).  The tile's fp32 values, exactly those
 // store_tile would write, are quantized in blocks of G (32, 64, 128 or 256) along each output row
 // by the quantizer's rule (codec.hpp), so the codes equal curvefp_quantize of curvefp_gemm_ws's C
-// with that block, bit for bit.  The tile goes through LDS (the freed stages) in four slices of
-// 64 rows: every wave writes its fp32 values of the slice (the 32 rows ti of both wave rows),
+// with that block, bit for bit.  Where K is split in two the sums are quantized by a second launch
+// (requant_slots_kernel, or the quantizer on the 128 x 128 tiles' C).  Where it is not, there is no room for C in the
+// workspace, and the tile goes through LDS (the freed stages) in four slices of 64 rows: every wave writes its fp32 values of the slice (the 32 rows ti of both wave rows),
 // then each thread quantizes two groups of 32 of the slice (a block's G/32 groups sit in
 // adjacent lanes and share its maximum) and stores their codes (32 contiguous bytes, or 28
 // packed) and the block's scale.
@@ -817,40 +818,97 @@ __device__ __forceinline__ int slice_off(int row, int col) {
     return row * 256 + ((((col >> 2) ^ (row & 7))) << 2) + (col & 3);
 }
 
-template <int BIAS2, bool ADD>
-__device__ __forceinline__ void requant_tile(f32x16 (&acc)[TM][4], const int* sAlpha, const int* sBeta,
-                                             int64_t M, int64_t N, int64_t m0, int64_t n0, int wm, int wn,
-                                             int lane, int tid, const char* other_slot, int wbase, char* slice_mem,
-                                             char* aux, const ReqOut& ro) {
-    constexpr int BN = 256, WN = Tile<256>::WN, TN = Tile<256>::TN;
-    float* slice = reinterpret_cast<float*>(slice_mem);          // 64 rows x 256 fp32 (64 KB)
-    // the output format's table behind one octave of rank-0 entries (base 0, threshold 0xFFFF):
-    // a magnitude scaled by ldexp lands in the pad or below it exactly when the quantizer's
-    // rule gives it rank 0, so the lookup needs no range tests
-    uint32_t* qlut = reinterpret_cast<uint32_t*>(aux);
+// the output format's table behind one octave of rank-0 entries (base 0, threshold 0xFFFF): a magnitude
+// scaled by ldexp lands in the pad or below it exactly when the quantizer's rule gives it rank 0, so the
+// lookup needs no range tests
+template <int THREADS>
+__device__ __forceinline__ void requant_table(uint32_t* qlut, const ReqOut& ro, int tid) {
+    for (int i = tid; i < ro.rule.qsize + 128; i += THREADS) qlut[i] = i < 128 ? 0xFFFFu : g_gq_lut[ro.fmt][i - 128];
+}
+
+// one lane's group of 32: row srow of the slice, its column group cb (group blk of output row `row`); the
+// G/32 groups of a block are adjacent lanes.  Groups past M or N hold zeros; blocks never straddle N
+// (N % G == 0), and every lane takes part in the block maximum before the invalid ones stop
+__device__ __forceinline__ void requant_group(const float* slice, int srow, int cb, int64_t row, int64_t blk, bool valid,
+                                              int64_t N, const uint32_t* qlut, const ReqOut& ro) {
     const QRule q = ro.rule;
-    __syncthreads();                                             // every wave is done with the stages
-    for (int i = tid; i < q.qsize + 128; i += NTHREADS) qlut[i] = i < 128 ? 0xFFFFu : g_gq_lut[ro.fmt][i - 128];
     const int ibase = (126 + q.oz) << 7, itop = q.qsize + 127;
-    const __amdgpu_buffer_rsrc_t rq =
-        __builtin_amdgcn_make_buffer_rsrc((void*)other_slot, (short)0, ADD ? (int)BM * BN * 4 : 0, 0x00020000);
+    const int64_t nbr = N / 32;                                  // groups per output row
+    // pass 1: the block maximum; pass 2: each 16-byte chunk (re-read from LDS) quantized and packed into
+    // the output words, so only one chunk is held at a time
+    const float* rowp = slice + srow * 256;
+    auto chunk = [&](int c) {
+        return *reinterpret_cast<const uint4*>(rowp + (((8 * cb + c) ^ (srow & 7)) << 2));
+    };
+    uint32_t amax = 0;
+#pragma unroll
+    for (int c = 0; c < 8; c++) {
+        const uint4 v = chunk(c);
+        amax = max(max(amax, max(v.x & 0x7FFFFFFFu, v.y & 0x7FFFFFFFu)), max(v.z & 0x7FFFFFFFu, v.w & 0x7FFFFFFFu));
+    }
+    for (int o = 1; o < (1 << ro.glog); o <<= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, o));
+    if (!valid) return;
+    const int a = qr_scale(amax, q);
+    // the packing is chosen once per group, so each loop below is straight-line code and its table lookups
+    // can be scheduled together
+    auto codes_of = [&](auto p7c) {
+        constexpr bool P7 = decltype(p7c)::value;
+        uint32_t wd[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < 8; c++) {
+            const uint4 v = chunk(c);
+            const uint32_t b4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                // |x| 2^-a by v_ldexp_f32: exact wherever it can reach a nonzero level (fp32 denormals are
+                // kept), below that it only needs to stay small
+                const uint32_t yb = __builtin_bit_cast(
+                    uint32_t, __builtin_amdgcn_ldexpf(__builtin_bit_cast(float, b4[j] & 0x7FFFFFFFu), -a));
+                const uint32_t e = qlut[min(max((int)(yb >> 16) - ibase, 0), itop)];
+                const uint32_t rk = (e >> 16) + (((yb & 0xFFFFu) > (e & 0xFFFFu)) ? 1u : 0u);
+                const uint32_t code = rk | ((rk != 0 ? b4[j] >> 31 : 0u) << q.ec);
+                if (!P7) {
+                    wd[c] |= code << (8 * j);
+                } else {
+                    const int bit = 7 * (4 * c + j);
+                    wd[bit >> 5] |= code << (bit & 31);
+                    if ((bit & 31) > 25) wd[(bit >> 5) + 1] |= code >> (32 - (bit & 31));
+                }
+            }
+        }
+        // a block that held a NaN or an infinity (scale -128) keeps zero codes
+        const uint32_t keep = a == -128 ? 0u : ~0u;
+#pragma unroll
+        for (int t = 0; t < 8; t++) wd[t] &= keep;
+        if (!P7) {
+            uint4* dst = reinterpret_cast<uint4*>(ro.codes + row * N + 32 * blk);
+            dst[0] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+            dst[1] = make_uint4(wd[4], wd[5], wd[6], wd[7]);
+        } else {
+            uint32_t* dst = reinterpret_cast<uint32_t*>(ro.codes + (row * nbr + blk) * 28);
+#pragma unroll
+            for (int j = 0; j < 7; j++) dst[j] = wd[j];
+        }
+    };
+    if (ro.packed7) codes_of(std::true_type());
+    else codes_of(std::false_type());
+    if ((cb & ((1 << ro.glog) - 1)) == 0) ro.scales[row * (nbr >> ro.glog) + (blk >> ro.glog)] = (int8_t)a;
+}
+
+template <int BIAS2>
+__device__ __forceinline__ void requant_tile(f32x16 (&acc)[TM][4], const int* sAlpha, const int* sBeta, int64_t M,
+                                             int64_t N, int64_t m0, int64_t n0, int wm, int wn, int lane, int tid,
+                                             char* slice_mem, char* aux, const ReqOut& ro) {
+    constexpr int WN = Tile<256>::WN, TN = Tile<256>::TN;
+    float* slice = reinterpret_cast<float*>(slice_mem);          // 64 rows x 256 fp32 (64 KB)
+    uint32_t* qlut = reinterpret_cast<uint32_t*>(aux);
+    __syncthreads();                                             // every wave is done with the stages
+    requant_table<NTHREADS>(qlut, ro, tid);
     const int lrow = 4 * (lane >> 5);                            // row of the lane within a 32-row block
     const int lcol = wn * WN + (lane & 31);
-    const int64_t nbr = N / 32;                                  // output blocks per row
 #pragma unroll
     for (int ti = 0; ti < TM; ti++) {
-        // phase A: this wave's 32 rows of slice ti (slice rows wm * 32 ..) into LDS; the other
-        // K half's sixteen partial vectors are all requested before the first is used
-        f32x4 other[TN][4];
-        if (ADD) {
-#pragma unroll
-            for (int tj = 0; tj < TN; tj++)
-#pragma unroll
-                for (int g = 0; g < 4; g++)
-                    other[tj][g] = __builtin_bit_cast(
-                        f32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, wbase + ((ti * 4 + tj) * 4 + g) * 1024, 0,
-                                                                     AUX_DEVICE_COHERENT));
-        }
+        // phase A: this wave's 32 rows of slice ti (slice rows wm * 32 ..) into LDS
 #pragma unroll
         for (int tj = 0; tj < TN; tj++) {
             const int beta = sBeta[lcol + 32 * tj] - BIAS2;
@@ -861,85 +919,72 @@ __device__ __forceinline__ void requant_tile(f32x16 (&acc)[TM][4], const int* sA
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
                     float val = __builtin_amdgcn_ldexpf(acc[ti][tj][4 * g + r], alr[r] + beta);
-                    if (ADD) val += other[tj][g][r];
                     val = poisoned(val, alr[r], beta + BIAS2);
                     slice[slice_off(wm * 32 + lrow + 8 * g + r, lcol + 32 * tj)] = val;
                 }
             }
         }
         __syncthreads();
-        // phase B: 64 rows x 8 groups of 32, two per thread (eight adjacent lanes cover one row,
-        // so a block of G = 32 << glog is G/32 adjacent lanes)
+        // phase B: 64 rows x 8 groups of 32, two per thread (eight adjacent lanes cover one row)
         for (int bi = tid; bi < 64 * 8; bi += NTHREADS) {
             const int srow = bi >> 3, cb = bi & 7;
             const int64_t row = m0 + (srow >> 5) * WM + 32 * ti + (srow & 31);
             const int64_t blk = n0 / 32 + cb;
-            // groups past M or N hold zeros; blocks never straddle N (N % G == 0), and every lane
-            // takes part in the block maximum before the invalid ones stop
-            const bool valid = row < M && blk < nbr;
-            // pass 1: the block maximum; pass 2: each 16-byte chunk (re-read from LDS) quantized
-            // and packed into the output words, so only one chunk is held at a time
-            const float* rowp = slice + srow * 256;
-            auto chunk = [&](int c) {
-                return *reinterpret_cast<const uint4*>(rowp + (((8 * cb + c) ^ (srow & 7)) << 2));
-            };
-            uint32_t amax = 0;
-#pragma unroll
-            for (int c = 0; c < 8; c++) {
-                const uint4 v = chunk(c);
-                amax = max(max(amax, max(v.x & 0x7FFFFFFFu, v.y & 0x7FFFFFFFu)),
-                           max(v.z & 0x7FFFFFFFu, v.w & 0x7FFFFFFFu));
-            }
-            for (int o = 1; o < (1 << ro.glog); o <<= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, o));
-            if (!valid) continue;
-            const int a = qr_scale(amax, q);
-            // the packing is chosen once per block, so each loop below is straight-line code and
-            // its table lookups can be scheduled together
-            auto codes_of = [&](auto p7c) {
-                constexpr bool P7 = decltype(p7c)::value;
-                uint32_t wd[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                for (int c = 0; c < 8; c++) {
-                    const uint4 v = chunk(c);
-                    const uint32_t b4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int j = 0; j < 4; j++) {
-                        // |x| 2^-a by v_ldexp_f32: exact wherever it can reach a nonzero level
-                        // (fp32 denormals are kept), below that it only needs to stay small
-                        const uint32_t yb = __builtin_bit_cast(
-                            uint32_t, __builtin_amdgcn_ldexpf(__builtin_bit_cast(float, b4[j] & 0x7FFFFFFFu), -a));
-                        const uint32_t e = qlut[min(max((int)(yb >> 16) - ibase, 0), itop)];
-                        const uint32_t rk = (e >> 16) + (((yb & 0xFFFFu) > (e & 0xFFFFu)) ? 1u : 0u);
-                        const uint32_t code = rk | ((rk != 0 ? b4[j] >> 31 : 0u) << q.ec);
-                        if (!P7) {
-                            wd[c] |= code << (8 * j);
-                        } else {
-                            const int bit = 7 * (4 * c + j);
-                            wd[bit >> 5] |= code << (bit & 31);
-                            if ((bit & 31) > 25) wd[(bit >> 5) + 1] |= code >> (32 - (bit & 31));
-                        }
-                    }
-                }
-                // a block that held a NaN or an infinity (scale -128) keeps zero codes
-                const uint32_t keep = a == -128 ? 0u : ~0u;
-#pragma unroll
-                for (int t = 0; t < 8; t++) wd[t] &= keep;
-                if (!P7) {
-                    uint4* dst = reinterpret_cast<uint4*>(ro.codes + row * N + 32 * blk);
-                    dst[0] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-                    dst[1] = make_uint4(wd[4], wd[5], wd[6], wd[7]);
-                } else {
-                    uint32_t* dst = reinterpret_cast<uint32_t*>(ro.codes + (row * nbr + blk) * 28);
-#pragma unroll
-                    for (int j = 0; j < 7; j++) dst[j] = wd[j];
-                }
-            };
-            if (ro.packed7) codes_of(std::true_type());
-            else codes_of(std::false_type());
-            if ((cb & ((1 << ro.glog) - 1)) == 0) ro.scales[row * (nbr >> ro.glog) + (blk >> ro.glog)] = (int8_t)a;
+            requant_group(slice, srow, cb, row, blk, row < M && blk < N / 32, N, qlut, ro);
         }
         __syncthreads();                                         // the slice is free for the next ti
     }
+}
+
+// K split in two: the GEMM's halves leave their scaled values in the tile's two slots and this kernel adds
+// them, in the order of either arrival (the sum is the same), and quantizes.  A wave takes 8 rows of a tile:
+// its 256 columns are 8 slot chunks of 1 KB (8 rows x 32 columns, coalesced) per half, all requested
+// before the first is used; they go through its own 8 KB of LDS, after which each lane holds one group of 32.
+// Bound by the slots' bytes (8 per output, 3.9 TB/s with the codes).  In the GEMM's epilogue the quantization
+// ran in one wave per SIMD and, as only the half that arrives second has the sum, in half of the
+// workgroups; 2048 x 4096 x 4096 E3C3, GEMM and requantization: 203 -> 171 + 17 us, 2048 x 2048 x 8192 the
+// whole call 275 -> 213, 2048 x 4096 x 1024 87 -> 74 us.
+constexpr int RQ_WAVES = 8;
+
+__global__ __launch_bounds__(64 * RQ_WAVES, 4) void requant_slots_kernel(const char* __restrict__ part,
+                                                                         const int* __restrict__ maxA,
+                                                                         const int* __restrict__ maxB, int64_t M,
+                                                                         int64_t N, uint32_t RTB, ReqOut ro) {
+    __shared__ __attribute__((aligned(16))) float slices[RQ_WAVES * 8 * 256];
+    extern __shared__ uint32_t qlut[];                           // the table: rule.qsize + 128 words
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tile = blockIdx.x / (32 / RQ_WAVES);
+    const int rs = (int)(blockIdx.x % (32 / RQ_WAVES)) * RQ_WAVES + wave;   // rows 8 rs .. 8 rs + 7 of the tile
+    const int64_t row0 = (int64_t)(tile / RTB) * BM + 8 * rs, n0 = (int64_t)(tile % RTB) * 256;
+    requant_table<64 * RQ_WAVES>(qlut, ro, tid);
+    __syncthreads();
+    if (row0 >= M) return;                                       // uniform per wave, and no barrier follows
+    const char* slot = part + (int64_t)tile * 2 * PART_BYTES + (rs >> 4) * 2 * 65536 + ((rs >> 2) & 3) * 16384 +
+                       (rs & 3) * 1024 + lane * 16;
+    f32x4 x[8], y[8];
+#pragma unroll
+    for (int c = 0; c < 8; c++) {                                // chunk c: columns 32 c .. 32 c + 31
+        const char* p = slot + (c >> 2) * 65536 + (c & 3) * 4096;
+        x[c] = *reinterpret_cast<const f32x4*>(p);
+        y[c] = *reinterpret_cast<const f32x4*>(p + PART_BYTES);
+    }
+    const int lrow = 4 * (lane >> 5), lcol = lane & 31;
+    const int4 al = *reinterpret_cast<const int4*>(maxA + row0 + lrow);
+    const int alr[4] = {al.x, al.y, al.z, al.w};
+    float* slice = slices + wave * 8 * 256;
+#pragma unroll
+    for (int c = 0; c < 8; c++) {
+        const int beta = maxB[n0 + 32 * c + lcol];
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+            slice[slice_off(lrow + r, 32 * c + lcol)] = poisoned(x[c][r] + y[c][r], alr[r], beta);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");        // the slice is this wave's alone: no barrier
+    __builtin_amdgcn_wave_barrier();
+    const int srow = lane >> 3, cb = lane & 7;
+    const int64_t row = row0 + srow, blk = n0 / 32 + cb;
+    requant_group(slice, srow, cb, row, blk, row < M && blk < N / 32, N, qlut, ro);
 }
 
 // GEMM on expanded planes: 256 x 256 tile per 256-thread workgroup as in the fused kernel (the
@@ -1131,7 +1176,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_ws_kernel(
 
     if (splits == 1) {
         if (REQ)
-            requant_tile<BIAS2, false>(acc, sAlpha, sBeta, M, N, m0, n0, wm, wn, lane, tid, nullptr, 0, st0, st1, ro);
+            requant_tile<BIAS2>(acc, sAlpha, sBeta, M, N, m0, n0, wm, wn, lane, tid, st0, st1, ro);
         else
             store_tile<BIAS2, BN>(acc, sAlpha, sBeta, C, ldc, M, N, m0, n0, wm, wn, lane, false);
         return;
@@ -1171,18 +1216,15 @@ __global__ __launch_bounds__(NTHREADS) void gemm_ws_kernel(
                 }
             }
     }
+    if (REQ) return;                      // requant_slots_kernel takes both slots
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's slot stores are complete
     __syncthreads();
     if (tid == 0)
         sLast[0] = __hip_atomic_fetch_add(cnt + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 1;
     __syncthreads();
     if (!sLast[0]) return;   // uniform: the other half arrives later and finishes the tile
-    if (REQ)
-        requant_tile<BIAS2, true>(acc, sAlpha, sBeta, M, N, m0, n0, wm, wn, lane, tid,
-                                  slots + (1 - wi.split) * PART_BYTES, wbase, st0, st1, ro);
-    else
-        store_tile<BIAS2, BN, true>(acc, sAlpha, sBeta, C, ldc, M, N, m0, n0, wm, wn, lane, false,
-                                    slots + (1 - wi.split) * PART_BYTES, wbase);
+    store_tile<BIAS2, BN, true>(acc, sAlpha, sBeta, C, ldc, M, N, m0, n0, wm, wn, lane, false,
+                                slots + (1 - wi.split) * PART_BYTES, wbase);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1480,8 +1522,10 @@ hipError_t launch_ws_fmt(const void* a, const int8_t* as, const void* b, const i
                                N, K, w.rta, w.rtb, c, ldc, splits, ws + w.part, cnt);
 }
 
-// curvefp_gemm_ws with its epilogue requantizing C (see requant_tile): the same prep and
-// expansion launches, then gemm_ws_kernel<BIAS2, true>
+// curvefp_gemm_ws with C requantized: the same prep and expansion launches, then the GEMM's epilogue
+// (requant_tile) quantizes, or a launch after it where K is split.  With the 128 x 128 tiles C (in the slots
+// they do not use, 256-byte aligned) goes through the quantizer: 512 x 4096 x 4096 149 -> 95 us, 1024 x 4096 x 4096
+// 161 -> 121, 1100 x 1088 x 4096 142 -> 85 us, the whole call against the 256 x 256 tiles' epilogue.
 template <class F>
 hipError_t launch_requant_fmt(const void* a, const int8_t* as, const void* b, const int8_t* bs, int64_t M,
                               int64_t N, int64_t K, int block, char* ws, int fidx, int ofmt, int oblock, uint8_t* qc,
@@ -1493,24 +1537,34 @@ hipError_t launch_requant_fmt(const void* a, const int8_t* as, const void* b, co
     int* maxB = reinterpret_cast<int*>(ws + w.max_b);
     const int64_t tiles = w.rta * w.rtb;
     const int splits = w.splits;
-    int* cnt = reinterpret_cast<int*>(ws + w.cnt);
     const int ga = (int)(w.rta * BM / 16), gb = (int)(w.rtb * BM / 16);
-    const int ncnt = splits > 1 ? (int)tiles : 0;
-    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)(ga + gb + (splits > 1 ? 1 : 0))), dim3(256), 0, s, as, bs, M, N,
-                       nsb, ga, gb, maxA, maxB, cnt, ncnt);
+    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)(ga + gb)), dim3(256), 0, s, as, bs, M, N, nsb, ga, gb, maxA, maxB,
+                       (int*)nullptr, 0);   // no arrivals are counted
     const ExpandOperand opA = {reinterpret_cast<const uint8_t*>(a), as, M, w.rta, maxA, ws + w.planes_a, fidx, nsb, dgq};
     const ExpandOperand opB = {reinterpret_cast<const uint8_t*>(b), bs, N, w.rtb, maxB, ws + w.planes_b, fidx, nsb, dgq};
     hipLaunchKernelGGL((expand_kernel<F>), dim3((unsigned)(4 * (w.rta + w.rtb)), (unsigned)((nkb + 3) / 4)),
                        dim3(256), 0, s, opA, opB, nkb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    char* part = ws + w.part;
+    if (splits > 1 && mid_tiles(M, N, K)) {
+        // the 128 x 128 tiles use no slots (two of 256 KB per 256 x 256 outputs): their C goes there
+        float* c = reinterpret_cast<float*>(part);
+        e = launch_gemm_mid(ws + w.planes_a, ws + w.planes_b, maxA, maxB, M, N, K, w.rta, w.rtb, c, N, 2 * F::GEMM_BIAS,
+                            splits, s);
+        if (e != hipSuccess) return e;
+        return launch_quantize(c, 0, M, N, N, 1, ofmt, oblock, qc, qs, s);
+    }
     int glog = 0;
     while ((32 << glog) < oblock) glog++;
     const ReqOut ro{qc, qs, qrule(ofmt), ofmt, ofmt == 2 ? 1 : 0, glog};
     const int64_t grid = (tiles * splits + 7) / 8 * 8;
     hipLaunchKernelGGL((gemm_ws_kernel<2 * F::GEMM_BIAS, true>), dim3((unsigned)grid), dim3(NTHREADS), 0, s,
-                       ws + w.planes_a, ws + w.planes_b, maxA, maxB, M, N, K, w.rta, w.rtb, nullptr, N, splits,
-                       ws + w.part, cnt, ro);
+                       ws + w.planes_a, ws + w.planes_b, maxA, maxB, M, N, K, w.rta, w.rtb, nullptr, N, splits, part,
+                       (int*)nullptr, ro);
+    if (splits > 1)
+        hipLaunchKernelGGL(requant_slots_kernel, dim3((unsigned)(tiles * (32 / RQ_WAVES))), dim3(64 * RQ_WAVES),
+                           (size_t)(ro.rule.qsize + 128) * 4, s, part, maxA, maxB, M, N, (uint32_t)w.rtb, ro);
     return hipGetLastError();
 }
 
