@@ -30,9 +30,11 @@
 // XOR-swizzled by ((row >> 1) ^ (row >> 3)) & 3, so fragment reads and
 // expansion writes spread over the banks.
 //
-// Small problems split K in two (grid.z = 2) so the grid covers the 256
-// compute units; the two partial sums land in C through fp32 atomic adds on
-// a zero-filled C, which is order-independent for two terms.
+// Products with fewer tiles than the 256 compute units split K in two
+// (grid.z = 2); the two partial sums land in C through fp32 atomic adds on
+// a zero-filled C, which is order-independent for two terms.  Small products
+// (small_plan) go to gemm_small.hip's kernels at every entry point, and
+// expanded planes to gemm_mid.hip's 128 x 128 tiles where mid_tiles says so.
 #include "codec.hpp"
 #include "curvefp_internal.hpp"
 #include "device_util.hpp"
@@ -797,8 +799,9 @@ __device__ __forceinline__ WorkItem work_item(int tiles_y, int tiles_x, int spli
 // store_tile would write, are quantized in blocks of G (32, 64, 128 or 256) along each output row
 // by the quantizer's rule (codec.hpp), so the codes equal curvefp_quantize of curvefp_gemm_ws's C
 // with that block, bit for bit.  Where K is split in two the sums are quantized by a second launch
-// (requant_slots_kernel, or the quantizer on the 128 x 128 tiles' C).  Where it is not, there is no room for C in the
-// workspace, and the tile goes through LDS (the freed stages) in four slices of 64 rows: every wave writes its fp32 values of the slice (the 32 rows ti of both wave rows),
+// (requant_slots_kernel, or the quantizer on the 128 x 128 tiles' C).  Where it is not, there is no
+// room for C in the workspace, and the tile goes through LDS (the freed stages) in four slices of
+// 64 rows: every wave writes its fp32 values of the slice (the 32 rows ti of both wave rows),
 // then each thread quantizes two groups of 32 of the slice (a block's G/32 groups sit in
 // adjacent lanes and share its maximum) and stores their codes (32 contiguous bytes, or 28
 // packed) and the block's scale.
@@ -940,7 +943,7 @@ __device__ __forceinline__ void requant_tile(f32x16 (&acc)[TM][4], const int* sA
 // them, in the order of either arrival (the sum is the same), and quantizes.  A wave takes 8 rows of a tile:
 // its 256 columns are 8 slot chunks of 1 KB (8 rows x 32 columns, coalesced) per half, all requested
 // before the first is used; they go through its own 8 KB of LDS, after which each lane holds one group of 32.
-// Bound by the slots' bytes (8 per output, 3.9 TB/s with the codes).  In the GEMM's epilogue the quantization
+// Bound by the slots' bytes (8 per output; 4.4 TB/s with the codes).  In the GEMM's epilogue the quantization
 // ran in one wave per SIMD and, as only the half that arrives second has the sum, in half of the
 // workgroups; 2048 x 4096 x 4096 E3C3, GEMM and requantization: 203 -> 171 + 17 us, 2048 x 2048 x 8192 the
 // whole call 275 -> 213, 2048 x 4096 x 1024 87 -> 74 us.
@@ -1667,8 +1670,8 @@ hipError_t launch_tile(const void* a, const int8_t* as, const void* b, const int
     return hipGetLastError();
 }
 
-// 256 x 256 tiles; K is split in two (partial sums added into a cleared C) when the tiles cover
-// fewer than the 256 compute units and K is long enough.  (256 x 128 tiles without a split
+// 256 x 256 tiles (products that small_plan does not take); K is split in two (partial sums added into a
+// cleared C) when the tiles cover fewer than the 256 compute units and K is long enough.  (256 x 128 tiles without a split
 // measured 17% slower on 2048 x 4096 x 4096.)
 template <class F>
 hipError_t launch_fmt(const void* a, const int8_t* as, const void* b, const int8_t* bs, int64_t M,

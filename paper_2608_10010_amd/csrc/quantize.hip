@@ -375,21 +375,27 @@ hipError_t launch_rows(const void* src, int64_t rows, int64_t cols, int64_t ld, 
     return launch_rows_u<F, BF16, 1>(src, rows, cols, ld, fidx, codes, scales, block, lgl, dgl, s);
 }
 
-// quantize-transpose through LDS: a workgroup takes 128 rows (four blocks) x 64 columns.  The
+// quantize-transpose through LDS: a workgroup takes 128 rows (four blocks) x 64 or 128 columns.  The
 // tile is read with 16-byte loads along the source rows, each thread then quantizes one
 // column's group of 32 from LDS (a wave reads one contiguous row segment per step; for blocks
 // of G > 32 rows the scale pass has written the block scales), and the
 // codes go back through LDS so every column's 128 code bytes (112 for E3C3) leave as whole
 // 16-byte stores.  Needs rows % 128 == 0, cols % 8 == 0 and a 16-byte aligned source.
-constexpr int TT_ROWS = 128, TT_COLS = 64;
+// bf16 to 8-bit codes: a group is quantized eight values at a time (135 -> 111 registers, 3 -> 4 waves per
+// SIMD), and tiles that form their scales are 128 columns wide, which fills the table half as often: 4096 x
+// 11008 E4C3 37.6 -> 34.6 us, 14336 x 4096 E5C2 55.3 -> 41.9, 32768 x 8192 E4C3 259 -> 239 (3.4 TB/s); with given
+// scales 64 columns are better (8192 x 14336, G = 64: 123 -> 117 us, 120 with 128).  For fp32 sources (the tile in
+// LDS holds them to 3 waves per SIMD) and 7-bit codes eight at a time measured 1-3% slower; they keep all 32
+// at once and 64 columns.
+constexpr int TT_ROWS = 128;
 constexpr int TT_OUT_STRIDE = 144;   // 128 code bytes + 16: the 16-byte writes of a wave spread over the banks
 
-template <class F, bool BF16>
-__global__ __launch_bounds__(256) void quantize_cols_tiled_kernel(
+template <class F, bool BF16, int TT_COLS>
+__global__ __launch_bounds__(4 * TT_COLS) void quantize_cols_tiled_kernel(
     const void* __restrict__ src, int64_t rows, int64_t cols, int64_t ld,
     uint8_t* __restrict__ codes, int8_t* __restrict__ scales, int fidx, int given, int64_t nsb, Div32 dgq) {
     using T = typename std::conditional<BF16, uint8_t, uint32_t>::type;
-    constexpr int ESZ = BF16 ? 2 : 4;
+    constexpr int ESZ = BF16 ? 2 : 4, THREADS = 4 * TT_COLS;   // a thread per column and block of 32 rows
     constexpr int SEG = TT_COLS * ESZ / 16;            // 16-byte pieces per tile row
     __shared__ __attribute__((aligned(16))) T lut[F::QLUT_SIZE];
     __shared__ __attribute__((aligned(16))) char tile[TT_ROWS * TT_COLS * ESZ];
@@ -400,10 +406,10 @@ __global__ __launch_bounds__(256) void quantize_cols_tiled_kernel(
     const int64_t c0 = (int64_t)blockIdx.x * TT_COLS, r0 = (int64_t)blockIdx.y * TT_ROWS;
     const char* s8 = reinterpret_cast<const char*>(src);
     // phase 1: the tile, 16 bytes per load (columns past the end are not read)
-    uint4 v[TT_ROWS * SEG / 256];
+    uint4 v[TT_ROWS * SEG / THREADS];
 #pragma unroll
-    for (int k = 0; k < TT_ROWS * SEG / 256; k++) {
-        const int piece = tid + 256 * k, row = piece / SEG, seg = piece % SEG;
+    for (int k = 0; k < TT_ROWS * SEG / THREADS; k++) {
+        const int piece = tid + THREADS * k, row = piece / SEG, seg = piece % SEG;
         const int64_t col = c0 + seg * (16 / ESZ);
         v[k] = col < cols ? ld16<true>(reinterpret_cast<const uint4*>(s8 + ((r0 + row) * ld + col) * ESZ))
                           : make_uint4(0, 0, 0, 0);
@@ -411,18 +417,18 @@ __global__ __launch_bounds__(256) void quantize_cols_tiled_kernel(
     if (BF16) {
         const uint32_t* s32 = reinterpret_cast<const uint32_t*>(g_qlut8[fidx]);
         uint32_t* l32 = reinterpret_cast<uint32_t*>(lut);
-        for (int i = tid; i < F::QLUT_SIZE / 4; i += 256) l32[i] = s32[i];
+        for (int i = tid; i < F::QLUT_SIZE / 4; i += THREADS) l32[i] = s32[i];
     } else {
-        for (int i = tid; i < F::QLUT_SIZE; i += 256) lut[i] = (T)g_qlut[fidx][i];
+        for (int i = tid; i < F::QLUT_SIZE; i += THREADS) lut[i] = (T)g_qlut[fidx][i];
     }
     const uint32_t lmax_mant = g_lmax_mant[fidx];
 #pragma unroll
-    for (int k = 0; k < TT_ROWS * SEG / 256; k++)
-        *reinterpret_cast<uint4*>(tile + (tid + 256 * k) * 16) = v[k];
+    for (int k = 0; k < TT_ROWS * SEG / THREADS; k++)
+        *reinterpret_cast<uint4*>(tile + (tid + THREADS * k) * 16) = v[k];
     __syncthreads();
 
     // phase 2: thread = (column j, block b)
-    const int j = tid & (TT_COLS - 1), b = tid >> 6;
+    const int j = tid & (TT_COLS - 1), b = (uint32_t)tid / TT_COLS;
     uint32_t mag[32], sgn[32];
 #pragma unroll
     for (int i = 0; i < 32; i++) {
@@ -441,32 +447,47 @@ __global__ __launch_bounds__(256) void quantize_cols_tiled_kernel(
         for (int i = 0; i < 32; i++) amax = max(amax, mag[i]);
         a = scale_of<F>(amax, lmax_mant);
     }
-    uint32_t rk[32];
-    ranks_of<F>(mag, 32, a, lut, rk);
-    uint32_t cc[32];
-#pragma unroll
-    for (int i = 0; i < 32; i++) cc[i] = rk[i] | ((rk[i] != 0 ? sgn[i] : 0u) << F::EC);
     uint8_t* ob = outb + j * TT_OUT_STRIDE;
-    if (!F::PACKED7) {
+    if constexpr (BF16 && !F::PACKED7) {
+        uint32_t o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int q = 0; q < 2; q++) {
-            const uint32_t* k = cc + 16 * q;
-            *reinterpret_cast<uint4*>(ob + b * 32 + 16 * q) =
-                make_uint4(k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24),
-                           k[4] | (k[5] << 8) | (k[6] << 16) | (k[7] << 24),
-                           k[8] | (k[9] << 8) | (k[10] << 16) | (k[11] << 24),
-                           k[12] | (k[13] << 8) | (k[14] << 16) | (k[15] << 24));
+        for (int g = 0; g < 4; g++) {
+            uint32_t rk[8];
+            ranks_of<F>(mag + 8 * g, 8, a, lut, rk);
+#pragma unroll
+            for (int i = 0; i < 8; i++)
+                o[2 * g + i / 4] |= (rk[i] | ((rk[i] != 0 ? sgn[8 * g + i] : 0u) << F::EC)) << (8 * (i & 3));
         }
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+            *reinterpret_cast<uint4*>(ob + b * 32 + 16 * q) = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
     } else {
-        uint32_t w[7] = {0, 0, 0, 0, 0, 0, 0};
+        uint32_t rk[32];
+        ranks_of<F>(mag, 32, a, lut, rk);
+        uint32_t cc[32];
 #pragma unroll
-        for (int i = 0; i < 32; i++) {
-            const int bit = 7 * i, d = bit >> 5, sh = bit & 31;
-            w[d] |= cc[i] << sh;
-            if (sh > 25) w[d + 1] |= cc[i] >> (32 - sh);
+        for (int i = 0; i < 32; i++) cc[i] = rk[i] | ((rk[i] != 0 ? sgn[i] : 0u) << F::EC);
+        if (!F::PACKED7) {
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                const uint32_t* k = cc + 16 * q;
+                *reinterpret_cast<uint4*>(ob + b * 32 + 16 * q) =
+                    make_uint4(k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24),
+                               k[4] | (k[5] << 8) | (k[6] << 16) | (k[7] << 24),
+                               k[8] | (k[9] << 8) | (k[10] << 16) | (k[11] << 24),
+                               k[12] | (k[13] << 8) | (k[14] << 16) | (k[15] << 24));
+            }
+        } else {
+            uint32_t w[7] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < 32; i++) {
+                const int bit = 7 * i, d = bit >> 5, sh = bit & 31;
+                w[d] |= cc[i] << sh;
+                if (sh > 25) w[d + 1] |= cc[i] >> (32 - sh);
+            }
+#pragma unroll
+            for (int d = 0; d < 7; d++) *reinterpret_cast<uint32_t*>(ob + b * 28 + 4 * d) = w[d];
         }
-#pragma unroll
-        for (int d = 0; d < 7; d++) *reinterpret_cast<uint32_t*>(ob + b * 28 + 4 * d) = w[d];
     }
     scl[j * 4 + b] = (int8_t)a;
     __syncthreads();
@@ -475,8 +496,8 @@ __global__ __launch_bounds__(256) void quantize_cols_tiled_kernel(
     constexpr int CB = F::PACKED7 ? 4 * 28 : 128;   // code bytes per column and tile
     const int64_t rblocks = rows / 32;
 #pragma unroll
-    for (int k = 0; k < (TT_COLS * CB / 16 + 255) / 256; k++) {
-        const int piece = tid + 256 * k;
+    for (int k = 0; k < (TT_COLS * CB / 16 + THREADS - 1) / THREADS; k++) {
+        const int piece = tid + THREADS * k;
         if (piece < TT_COLS * CB / 16) {
             const int jj = piece / (CB / 16), qq = piece % (CB / 16);
             const int64_t col = c0 + jj;
@@ -491,6 +512,27 @@ __global__ __launch_bounds__(256) void quantize_cols_tiled_kernel(
         const int jj = tid >> 2, bb = tid & 3;
         if (c0 + jj < cols) scales[(c0 + jj) * rblocks + r0 / 32 + bb] = scl[jj * 4 + bb];
     }
+}
+
+template <class F, bool BF16, int COLS>
+void launch_cols_tiled(const void* src, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes, int8_t* scales, int fidx,
+                       int given, int64_t nsb, Div32 dgq, hipStream_t s) {
+    const dim3 grid((unsigned)((cols + COLS - 1) / COLS), (unsigned)(rows / TT_ROWS));
+    hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, BF16, COLS>), grid, dim3(4 * COLS), 0, s, src, rows, cols, ld, codes,
+                       scales, fidx, given, nsb, dgq);
+}
+
+// the tile's width: see quantize_cols_tiled_kernel
+template <class F>
+hipError_t launch_cols_tiled(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
+                             int8_t* scales, int fidx, int given, int64_t nsb, Div32 dgq, hipStream_t s) {
+    if (dtype != 1)
+        launch_cols_tiled<F, false, 64>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    else if (F::PACKED7 || given)
+        launch_cols_tiled<F, true, 64>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    else
+        launch_cols_tiled<F, true, F::PACKED7 ? 64 : 128>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    return hipGetLastError();
 }
 
 // given != 0: the block scales (blocks of `block` rows) are already in `scales`
@@ -550,14 +592,7 @@ hipError_t launch_fmt(const void* src, int dtype, int64_t rows, int64_t cols, in
     const bool tiled = rows % TT_ROWS == 0 && cols % 8 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0 &&
                        (ld * esz) % 16 == 0 && rows / TT_ROWS <= 65535;
     if (tiled) {
-        const dim3 grid((unsigned)((cols + TT_COLS - 1) / TT_COLS), (unsigned)(rows / TT_ROWS));
-        if (dtype == 1)
-            hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, true>), grid, dim3(256), 0, s, src, rows, cols, ld, cp,
-                               scales, fidx, given, rows / block, dgq);
-        else
-            hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, false>), grid, dim3(256), 0, s, src, rows, cols, ld, cp,
-                               scales, fidx, given, rows / block, dgq);
-        return hipGetLastError();
+        return launch_cols_tiled<F>(src, dtype, rows, cols, ld, cp, scales, fidx, given, rows / block, dgq, s);
     }
     return launch_cols<F, 1>(src, dtype, rows, cols, ld, fidx, cp, scales, block, given, s);
 }
@@ -902,14 +937,7 @@ hipError_t launch_tensorwise_fmt(const void* src, int dtype, int64_t rows, int64
     const bool tiled = rows % TT_ROWS == 0 && cols % 8 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0 &&
                        (ld * esz) % 16 == 0 && rows / TT_ROWS <= 65535;
     if (tiled) {
-        const dim3 grid((unsigned)((cols + TT_COLS - 1) / TT_COLS), (unsigned)(rows / TT_ROWS));
-        if (dtype == 1)
-            hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, true>), grid, dim3(256), 0, s, src, rows, cols, ld, cp,
-                               scales, fidx, 1, (int64_t)1, dgq);
-        else
-            hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, false>), grid, dim3(256), 0, s, src, rows, cols, ld, cp,
-                               scales, fidx, 1, (int64_t)1, dgq);
-        return hipGetLastError();
+        return launch_cols_tiled<F>(src, dtype, rows, cols, ld, cp, scales, fidx, 1, (int64_t)1, dgq, s);
     }
     return launch_cols<F, 1>(src, dtype, rows, cols, ld, fidx, cp, scales, (int)rows, 1, s);
 }
