@@ -151,7 +151,8 @@ int curvefp_quantize_mse(const void* src, int dtype, int64_t rows, int64_t cols,
  * takes the operand as rowwise-scaled (block = the blocked extent).  A NaN or infinity
  * anywhere poisons the tensor (scale -128, zero codes).
  *   workspace  one 32-bit word of device memory (4-byte aligned), scratch of the call:
- *              calls that share it must be ordered.
+ *              calls that share it must be ordered.  (The partial maxima are kept in the code
+ *              buffer until the codes overwrite them.)
  * The blocked extent must be a multiple of 32 and at most 2^30 (CURVEFP_ERR_SHAPE).  The source
  * is read twice (its maximum, then the codes).
  */
@@ -248,7 +249,8 @@ int curvefp_dequantize(const void* codes, const int8_t* scales, int format,
  *
  * This entry point allocates nothing: the expansion happens inside the GEMM
  * kernel, once per workgroup that needs a code.  curvefp_gemm_ws below does the
- * expansion once per code and is faster; both give the same C bit for bit.
+ * expansion once per code and is faster on all but small products, where both
+ * take the same kernel; both give the same C bit for bit.
  */
 int curvefp_gemm(const void* a_codes, const int8_t* a_scales,
                  const void* b_codes, const int8_t* b_scales,
@@ -271,7 +273,9 @@ int64_t curvefp_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * of at least curvefp_gemm_workspace_bytes(M, N, K) bytes, 256-byte aligned.
  * The codes of A and B are first expanded once into fp16 high/low planes in
  * the workspace; the GEMM kernel then streams those planes into LDS and spends
- * its main loop on the matrix cores.  The workspace contents are scratch:
+ * its main loop on the matrix cores.  (Products with few outputs for their K are
+ * instead computed from the codes in one launch, at every entry point with the
+ * same order of sums.)  The workspace contents are scratch:
  * calls that share a workspace must be ordered (same stream, or synchronized).
  * Errors as curvefp_gemm, plus CURVEFP_ERR_NULL for a null workspace,
  * CURVEFP_ERR_SHAPE if workspace_bytes is too small and CURVEFP_ERR_ALIGN if
@@ -419,7 +423,7 @@ int curvefp_gemm_ws_static(const void* a_codes, const int8_t* a_scales,
 
 /*
  * The product of curvefp_gemm_ws (same operands, format, workspace and fp32 values), with
- * the output requantized in the GEMM's epilogue instead of stored as fp32: the explicit
+ * the output requantized on the device instead of returned as fp32: the explicit
  * output requantization of Sec. 3.2 (products are closed on widened coordinates; only the
  * requantization to a finite destination may saturate).  C is quantized in blocks of
  * out_block consecutive outputs along each row into out_format with the rule of
