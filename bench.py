@@ -105,20 +105,39 @@ def parse():
 
 
 COPY_BYTES = 256 << 20
-KERNEL_SOURCES = ("gemm.hip", "curvefp_internal.hpp", "device_util.hpp", "planes.hpp", "codec.hpp")
+CSRC = os.path.join(ROOT, "paper_2608_10010_amd", "csrc")
+GENERATED = {"curvefp_tables.inc": "gen_tables.cpp"}   # written at build time by this file's program
 
 
-QUANTIZE_SOURCES = ("quantize.hip", "curvefp_internal.hpp", "device_util.hpp", "planes.hpp", "codec.hpp")
+def sources_of(*mains):
+    """The files of csrc that make up these kernels: the given ones and every file that they include,
+    directly or not (for a generated file, its generator; a header brings the .cpp of its name)."""
+    found, todo = set(), list(mains)
+    while todo:
+        name = GENERATED.get(todo[-1], todo[-1])
+        todo.pop()
+        path = os.path.join(CSRC, name)
+        if name in found or not os.path.exists(path):
+            continue
+        found.add(name)
+        todo += re.findall(r'^\s*#\s*include\s+"([^"]+)"', open(path).read(), re.M)
+        todo.append(os.path.splitext(name)[0] + ".cpp")
+    return tuple(sorted(found))
+
+
+# the 256 x 256 kernel whose traffic is committed, and the kernels and rules beside it that decide whether it runs
+KERNEL_SOURCES = ("gemm.hip", "gemm_mid.hip", "gemm_small.hip")
+QUANTIZE_SOURCES = ("quantize.hip",)
 STREAM_TRAFFIC = os.path.join(ROOT, "profiles", "quantize_stream_e4c3_1gib_traffic.md")
 
 
 def kernel_source_digest(sources=None) -> str:
-    """sha256 over a kernel's sources (the GEMM's by default): a traffic figure is void once
-    they change."""
+    """sha256 over a kernel's sources (the GEMM's by default) and all that they include: a traffic figure is
+    void once they change."""
     import hashlib
     h = hashlib.sha256()
-    for name in (sources or KERNEL_SOURCES):
-        with open(os.path.join(ROOT, "paper_2608_10010_amd", "csrc", name), "rb") as f:
+    for name in sources_of(*(sources or KERNEL_SOURCES)):
+        with open(os.path.join(CSRC, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 

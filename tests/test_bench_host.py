@@ -141,6 +141,41 @@ def test_traffic_void_when_sources_change(monkeypatch):
     assert bench.measured_stream_traffic() is None
 
 
+@pytest.mark.parametrize("mains", [bench.KERNEL_SOURCES, bench.QUANTIZE_SOURCES], ids=lambda m: m[0])
+def test_digest_covers_what_the_compiler_reads(mains):
+    """Every file of csrc that the compiler opens for a kernel (its own dependency list) is in the digest, the
+    generated tables by the files that make them."""
+    from paper_2608_10010_amd import build
+    assert os.path.exists(build.TABLES_INC), "the library has not been built"
+    read = set()
+    for name in mains:
+        r = subprocess.run(["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-M", "-I", build.GEN_DIR,
+                            os.path.join(bench.CSRC, name)], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr
+        files = r.stdout.replace("\\\n", " ").split()
+        read |= {os.path.basename(f) for f in files if os.path.dirname(os.path.abspath(f)) == bench.CSRC}
+        if build.TABLES_INC in files:
+            read |= {"gen_tables.cpp", "tables.cpp"}
+    assert set(mains) < read
+    assert read <= set(bench.sources_of(*mains))
+
+
+def test_digest_changes_with_included_rules(monkeypatch, tmp_path):
+    """The quantizer's rules are in a header of their own: a change there voids the quantizer's figure."""
+    import shutil
+    csrc = tmp_path / "csrc"
+    shutil.copytree(bench.CSRC, csrc)
+    monkeypatch.setattr(bench, "CSRC", str(csrc))
+    before = bench.kernel_source_digest(bench.QUANTIZE_SOURCES)
+    with open(csrc / "quantize_rules.hpp", "a") as f:
+        f.write("// changed\n")
+    assert bench.kernel_source_digest(bench.QUANTIZE_SOURCES) != before
+    before = bench.kernel_source_digest()
+    with open(csrc / "gemm_small.hip", "a") as f:
+        f.write("// changed\n")
+    assert bench.kernel_source_digest() != before
+
+
 def test_profile_commands_are_the_bench_commands():
     """The committed counter summaries name the commands bench.py would give for them today."""
     for name in ("gemm_prepared_sweep8b_gateup_e4c3_8192x14336x4096_traffic.md",
