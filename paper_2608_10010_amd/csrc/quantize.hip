@@ -776,8 +776,12 @@ __global__ __launch_bounds__(256) void quantize_compact_rows_kernel(const void* 
         unpack8<BF16>(v[u], mag, sgn);
         encode_chunk<F, true>(mag, sgn, ae, c, lut, rc);
     }
-    if (WPR > 1) __syncthreads();
-    else __builtin_amdgcn_wave_barrier();              // doff is the wave's own
+    if (WPR > 1) {
+        __syncthreads();
+    } else {   // doff is the wave's own: its lanes' writes ordered before the other lanes' reads, no barrier
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     if (!live) return;
     // the offsets, one output byte per lane and step
     const int nb = (int)(cpr >> lgl);
