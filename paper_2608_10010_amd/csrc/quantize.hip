@@ -395,16 +395,12 @@ hipError_t launch_rows(const void* src, int64_t rows, int64_t cols, int64_t ld, 
 // of G > 32 rows the scale pass has written the block scales), and the
 // codes go back through LDS so every column's 128 code bytes (112 for E3C3) leave as whole
 // 16-byte stores.  Needs rows % 128 == 0, cols % 8 == 0 and a 16-byte aligned source.
-// bf16 to 8-bit codes: a group is quantized eight values at a time (135 -> 111 registers, 3 -> 4 waves per
-// SIMD), and tiles that form their scales are 128 columns wide, which fills the table half as often: 4096 x
-// 11008 E4C3 37.6 -> 34.6 us, 14336 x 4096 E5C2 55.3 -> 41.9, 32768 x 8192 E4C3 259 -> 239 (3.4 TB/s); with given
-// scales 64 columns are better (8192 x 14336, G = 64: 123 -> 117 us, 120 with 128).  For fp32 sources (the tile in
-// LDS holds them to 3 waves per SIMD) and 7-bit codes eight at a time measured 1-3% slower; they keep all 32
-// at once and 64 columns.
+// EIGHT: a group is quantized eight values at a time and not 32 (111 registers for 135: 4 waves per SIMD, 3
+// without).  Which form and width run: launch_cols_tiled.
 constexpr int TT_ROWS = 128;
 constexpr int TT_OUT_STRIDE = 144;   // 128 code bytes + 16: the 16-byte writes of a wave spread over the banks
 
-template <class F, bool BF16, int TT_COLS>
+template <class F, bool BF16, int TT_COLS, bool EIGHT>
 __global__ __launch_bounds__(4 * TT_COLS) void quantize_cols_tiled_kernel(
     const void* __restrict__ src, int64_t rows, int64_t cols, int64_t ld,
     uint8_t* __restrict__ codes, int8_t* __restrict__ scales, int fidx, int given, int64_t nsb, Div32 dgq) {
@@ -462,7 +458,8 @@ __global__ __launch_bounds__(4 * TT_COLS) void quantize_cols_tiled_kernel(
         a = scale_of<F>(amax, lmax_mant);
     }
     uint8_t* ob = outb + j * TT_OUT_STRIDE;
-    if constexpr (BF16 && !F::PACKED7) {
+    if constexpr (EIGHT) {
+        static_assert(!F::PACKED7, "whole bytes");
         uint32_t o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int g = 0; g < 4; g++) {
@@ -528,25 +525,33 @@ __global__ __launch_bounds__(4 * TT_COLS) void quantize_cols_tiled_kernel(
     }
 }
 
-template <class F, bool BF16, int COLS>
-void launch_cols_tiled(const void* src, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes, int8_t* scales, int fidx,
-                       int given, int64_t nsb, Div32 dgq, hipStream_t s) {
+template <class F, bool BF16, int COLS, bool EIGHT>
+hipError_t launch_cols_tile(const void* src, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes, int8_t* scales,
+                            int fidx, int given, int64_t nsb, Div32 dgq, hipStream_t s) {
     const dim3 grid((unsigned)((cols + COLS - 1) / COLS), (unsigned)(rows / TT_ROWS));
-    hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, BF16, COLS>), grid, dim3(4 * COLS), 0, s, src, rows, cols, ld, codes,
-                       scales, fidx, given, nsb, dgq);
+    hipLaunchKernelGGL((quantize_cols_tiled_kernel<F, BF16, COLS, EIGHT>), grid, dim3(4 * COLS), 0, s, src, rows, cols,
+                       ld, codes, scales, fidx, given, nsb, dgq);
+    return hipGetLastError();
 }
 
-// the tile's width: see quantize_cols_tiled_kernel
+// Up to 768 tiles of 64 columns are one round of the chip in the 32-at-once form (three tiles share a unit), which
+// is then the shortest: a tile's own time counts, and 128 columns leave units idle.  Beyond that, bf16 sources to
+// 8-bit codes take eight values at a time, in tiles of 128 columns (the table is filled half as often) or, where the
+// scale pass has written the scales, of 64.  bf16, 32 at once x 64 / eight x 64 / eight x 128: 512 x 4096 E4C3 4.5 /
+// 4.6 / 5.2 us, 1536 x 4096 (768 tiles) 7.0 / 7.1 / 7.9, 1792 x 4096 9.6 / 8.3 / 8.0, 4096 x 4096 17.0 / 14.9 / 14.5, 8192 x
+// 14336 E5C2 109 / 98 / 82; with given scales (G = 64) 1536 x 4096 8.5 / 8.7 / 10.6, 2048 x 4096 11.2 / 10.2 / 11.6,
+// 8192 x 14336 E4C3 125 / 117 / 123.  For fp32 sources (the tile in LDS holds them to 3 waves per SIMD) and 7-bit
+// codes eight at a time measured 1-3% slower at every size.
 template <class F>
 hipError_t launch_cols_tiled(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                              int8_t* scales, int fidx, int given, int64_t nsb, Div32 dgq, hipStream_t s) {
-    if (dtype != 1)
-        launch_cols_tiled<F, false, 64>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
-    else if (F::PACKED7 || given)
-        launch_cols_tiled<F, true, 64>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
-    else
-        launch_cols_tiled<F, true, F::PACKED7 ? 64 : 128>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
-    return hipGetLastError();
+    if (dtype != 1) return launch_cols_tile<F, false, 64, false>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    if constexpr (!F::PACKED7) {
+        if ((cols + 63) / 64 * (rows / TT_ROWS) > 768)
+            return given ? launch_cols_tile<F, true, 64, true>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s)
+                         : launch_cols_tile<F, true, 128, true>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    }
+    return launch_cols_tile<F, true, 64, false>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
 }
 
 // given != 0: the block scales (blocks of `block` rows) are already in `scales`

@@ -1,5 +1,6 @@
 """Quantize-transpose tiles of 64 and 128 columns: column counts at the edges of both widths, one and several
-tiles of 128 rows, a row stride, scales formed in the tile (G = 32) and given to it, blocks near the ends of
+tiles of 128 rows, both sides of the count of tiles (768 of 64 columns) from which bf16 sources take the form that
+quantizes eight values at a time, a row stride, scales formed in the tile (G = 32) and given to it, blocks near the ends of
 fp32's range and non-finite blocks; codes and scales equal to those of the transposed source quantized along
 its rows."""
 
@@ -15,7 +16,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,cols,G", [(128, 8, 32), (128, 56, 32), (256, 64, 64), (128, 72, 32), (384, 120, 128),
-                                         (128, 128, 32), (256, 136, 32), (256, 264, 64)])
+                                         (128, 128, 32), (256, 136, 32), (256, 264, 64),
+                                         (12288, 512, 32), (12288, 520, 32), (8192, 776, 64), (98432, 56, 32),
+                                         (7168, 896, 32), (7168, 888, 64)])
 def test_columns(fmt, dtype, rows, cols, G):
     say(f"[transpose tiles] {fmt} {dtype} {rows} x {cols} G={G}")
     g = torch.Generator(device=DEV).manual_seed(rows + cols)
