@@ -336,10 +336,11 @@ __global__ __launch_bounds__(256) void block_scales_cols_kernel(const void* __re
     }
 }
 
-// NT: streaming loads.  fp32 sources: at most 4096 workgroups, each looping, and plain loads (the table is
-// twice to four times bfloat16's, so more and shorter workgroups spend their time filling it: 4000 x 11008 to
-// E5C2 58.7 us with up to 32768 workgroups, 46.8 with 4096; 8192 x 14336 147 and 113 us).  bfloat16: up to
-// 32768 (4096 measured 2-9% faster on E5C2, 4% slower on 32768 x 8192 and on E3C3).
+// NT: streaming loads.  Each workgroup fills the table first, so fp32 sources (their table is two to four times
+// bfloat16's) run in workgroups of about two rounds, at least 4096 and at most 32768 of them, and take plain loads.  One
+// round each / 4096 at every size / this rule, E4C3: 4000 x 11008 46.0 / 38.4 / 38.4 us, 8192 x 14336 120 / 111 / 103,
+// 32768 x 8192 227 / 255 / 228, 32768 x 14336 (E3C3) 433 / 480 / 426.  bfloat16: up to 32768 (4096 measured 2-9%
+// faster on E5C2, 4% slower on 32768 x 8192 and on E3C3).
 template <class F, bool BF16, int U, bool NT = BF16>
 hipError_t launch_rows_u(const void* src, int64_t rows, int64_t cols, int64_t ld, int fidx, uint8_t* codes,
                          int8_t* scales, int block, int lgl, Div32 dgl, hipStream_t s) {
@@ -350,8 +351,8 @@ hipError_t launch_rows_u(const void* src, int64_t rows, int64_t cols, int64_t ld
         const int64_t nr = rows - r0 < slab ? rows - r0 : slab;
         const int64_t nchunks = nr * cpr;
         int64_t blocks = (nchunks + 256 * U - 1) / (256 * U);
-        constexpr int64_t MOST = BF16 ? 32768 : 4096;
-        blocks = blocks < MOST ? blocks : MOST;
+        if (!BF16 && blocks > 4096) blocks = blocks > 8192 ? (blocks + 1) / 2 : 4096;
+        blocks = blocks < 32768 ? blocks : 32768;
         const void* sp = reinterpret_cast<const char*>(src) + r0 * ld * (BF16 ? 2 : 4);
         uint8_t* cp = codes + (F::PACKED7 ? r0 * (cols / 32) * 28 : r0 * cols);
         int8_t* scp = scales + r0 * (cols / block);
