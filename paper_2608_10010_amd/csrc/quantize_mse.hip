@@ -12,7 +12,10 @@
 // candidate out before it is evaluated (sums of non-negative terms never fall, rounded or not).  Of normally
 // distributed weights four blocks in five stop there.  The (block, candidate) pairs left are collected in LDS
 // and shared out over the workgroup's threads, so that a wave evaluates 64 of them and not the few of its own
-// blocks; the blocks whose scale moved are written again in the same way.
+// blocks; the blocks whose scale moved are written again in the same way.  A scale above the ceil-absmax scale clips
+// nothing, so nothing rules it out: every thread evaluates those of its own block, before the others, from the
+// registers that hold it (from the list, E4C3 with radix 2^(3/4), fp32, blocks of 32 took 527 us for 8192 x 8192 and one
+// candidate, 331 from the registers).
 //
 // What bounds it: vector instructions (about 25 per element and candidate evaluated).  4096 x 4096 bf16 to
 // E3C3, four candidates, blocks of 32 / 64 / 512: 132 / 142 / 748 -> 46 / 50 / 155 us.
@@ -292,6 +295,7 @@ __global__ __launch_bounds__(256, HELD == 2 ? 2 : 3) void quantize_mse_kernel(Bl
     };
     bool live = false;
     double acc = 0.0;
+    int first_c = 0;   // the best of candidate 0 and those above it
     if (exists) {
         Group<BF16> held[HELD ? HELD : 1];
         uint32_t amax = 0;
@@ -316,9 +320,27 @@ __global__ __launch_bounds__(256, HELD == 2 ? 2 : 3) void quantize_mse_kernel(Bl
             for (int g = 0; g < groups; g++)
                 for (int d = 0; d < GB / 4; d++) reinterpret_cast<uint32_t*>(out + (int64_t)g * GB)[d] = 0;
         }
+        if (F::PERIOD > 1 && live) {
+#pragma unroll 1   // (all in one pass over the elements: the sums and codes together spill, twice the time)
+            for (int c = candidates; c < candidates + F::PERIOD - 1; c++) {
+                const int a = ac + c - candidates + 1;
+                if (a > 127) break;
+                double e = 0.0;
+                if (HELD && plain_scale<F>(a)) {
+#pragma unroll
+                    for (int g = 0; g < HELD; g++) group_plain<F, BF16, true, false>(tb, held[g], a, e, nullptr);
+                } else {
+                    evaluate(at, a, e, nullptr, std::true_type(), std::false_type());
+                }
+                if (e < acc) {
+                    acc = e;
+                    first_c = c;
+                }
+            }
+        }
     }
     best[tid] = acc;
-    best_c[tid] = 0;
+    best_c[tid] = (int8_t)first_c;
 
     auto scale_at = [&](int blk, int c) { return (int)ceil_a[blk] + (c < candidates ? -c : c - candidates + 1); };
     // the threads with `want` put their block on the list, and `work` runs once for each, spread over all
@@ -331,18 +353,18 @@ __global__ __launch_bounds__(256, HELD == 2 ? 2 : 3) void quantize_mse_kernel(Bl
         if (tid == 0) count = 0;
         __syncthreads();
     };
-    const int nc = candidates + F::PERIOD - 1;
-    for (int c = 1; c < nc; c++) {
+    // sum e of candidate c < candidates against a block's best so far: the first in order with the least sum wins, and
+    // the candidates above the ceil-absmax scale come after c
+    auto wins = [&](double e, int blk) {
+        return e < best[blk] || (F::PERIOD > 1 && e == best[blk] && best_c[blk] >= candidates);
+    };
+    for (int c = 1; c < candidates; c++) {
         bool want = false;
         if (live) {
             const int a = scale_at(tid, c);
-            if (a >= -127 && a <= 127) {
-                double least = 0.0;   // a bound on the candidate's sum
-                if (c < candidates) {
-                    const uint32_t v = value_bits<F>(F::NMAG - 1, a, tb.mant, tb.sig);
-                    least = add_square(0.0, f64_of(top_mag[tid]) - f64_of(v));
-                }
-                want = least < best[tid];
+            if (a >= -127) {
+                const uint32_t v = value_bits<F>(F::NMAG - 1, a, tb.mant, tb.sig);
+                want = wins(add_square(0.0, f64_of(top_mag[tid]) - f64_of(v)), tid);   // a bound on the candidate's sum
             }
         }
         share_out(want, [&](int blk) {
@@ -350,7 +372,7 @@ __global__ __launch_bounds__(256, HELD == 2 ? 2 : 3) void quantize_mse_kernel(Bl
             const int a = scale_at(blk, c);
             double e = 0.0;
             evaluate(o, a, e, nullptr, std::true_type(), std::false_type());
-            if (e < best[blk]) {
+            if (wins(e, blk)) {
                 best[blk] = e;
                 best_c[blk] = (int8_t)c;
             }
@@ -369,10 +391,13 @@ __global__ __launch_bounds__(256, HELD == 2 ? 2 : 3) void quantize_mse_kernel(Bl
 template <class F, bool BF16>
 hipError_t launch_held(const Blocks& s, int candidates, uint8_t* codes, int8_t* scales, int fidx, hipStream_t st) {
     const dim3 grid((unsigned)((s.nb + 255) / 256));
+    // 64 fp32 elements in registers leave one wave per SIMD: slower than reading again, unless every block is evaluated
+    // at two scales more (radix 2^(3/4), 8192 x 8192 along the rows: 498 us for 613; down the columns 394 for 321)
+    constexpr int HELD64 = BF16 || F::PERIOD > 1 ? 2 : 0;
     if (s.G == 32)
         hipLaunchKernelGGL((quantize_mse_kernel<F, BF16, 1>), grid, dim3(256), 0, st, s, candidates, codes, scales, fidx);
-    else if (BF16 && s.G == 64)   // 64 fp32 elements in registers leave one wave per SIMD: slower than reading again
-        hipLaunchKernelGGL((quantize_mse_kernel<F, BF16, BF16 ? 2 : 0>), grid, dim3(256), 0, st, s, candidates, codes, scales, fidx);
+    else if (HELD64 == 2 && s.G == 64 && (BF16 || s.axis == 1))
+        hipLaunchKernelGGL((quantize_mse_kernel<F, BF16, HELD64>), grid, dim3(256), 0, st, s, candidates, codes, scales, fidx);
     else
         hipLaunchKernelGGL((quantize_mse_kernel<F, BF16, 0>), grid, dim3(256), 0, st, s, candidates, codes, scales, fidx);
     return hipGetLastError();

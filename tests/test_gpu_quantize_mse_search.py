@@ -26,3 +26,27 @@ def test_search(fmt, dtype, G):
     say(f"[quantize_mse] search fmt={fmt} dtype={dtype} G={G}")
     run_and_compare(x, fmt, dtype, 1, 8, f"search {fmt} {dtype} G={G}", block=G)
     run_and_compare(np.ascontiguousarray(x.T), fmt, dtype, 0, 8, f"search {fmt} {dtype} G={G} axis0", block=G)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("G,candidates", [(32, 1), (32, 2), (64, 4), (96, 8)])
+def test_candidates_above_and_ties(dtype, G, candidates):
+    """Radix 2^(3/4): scales three apart share their levels.  Blocks of values near the levels of a scale whose top
+    lies just under the block's maximum: the scale below ceil-absmax and the second above it reconstruct alike, and the
+    one below, earlier in the order, wins; with one candidate the one above does.  Beside them blocks whose best scale is
+    ceil-absmax or the first above it, and blocks at the ends of the scale range."""
+    rng = np.random.default_rng(G + candidates)
+    n = rng.integers(-31, 63, (771, G))
+    n[:, 0] = 63
+    x = np.exp2(3.0 * n / 32) * (1 + rng.uniform(-2.0 ** -8, 2.0 ** -8, n.shape))
+    x[:, 0] = np.exp2(3.0 * 63 / 32) * (1 + 2.0 ** -7)
+    x *= np.where(rng.random(n.shape) < 0.5, -1.0, 1.0)
+    x[1::4] *= 2.0 ** -0.25                                   # off that scale's levels
+    x[2::4, 0] *= 1.0 - 2.0 ** -5                             # the maximum under the top: ceil-absmax itself
+    x[3::4, G // 2:] *= 2.0 ** -6                             # small values below the lower scales' range
+    x *= np.exp2(rng.integers(-3, 4, (771, 1)))
+    x[768] *= 2.0 ** -132                                     # subnormal maxima, and a maximum near fp32's
+    x[769] *= 2.0 ** -125
+    x[770] *= 2.0 ** 112
+    say(f"[quantize_mse] above and ties dtype={dtype} G={G} candidates={candidates}")
+    run_and_compare(x.astype(np.float32), "E4C3_r3/4", dtype, 1, candidates, f"ties {dtype} G={G}", block=G)
