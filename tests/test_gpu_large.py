@@ -1,7 +1,7 @@
 """GPU edge cases at the limits of the index arithmetic: a row quantization and a
 dequantization whose chunk count passes one launch's 32-bit range (the launches are cut
 into slabs), a GEMM with K = 2^20, and outputs whose row stride exceeds 2^20 floats
-(the GEMM epilogue then takes its 64-bit addressing path, with and without a K split).
+(a small product here; larger ones in test_gpu_gemm_routes).
 Outputs are checked against the oracle on sampled rows; the largest case needs about
 90 GB of device memory and is skipped when that is not free."""
 
@@ -66,7 +66,7 @@ def test_gemm_long_k():
     say(f"[large] K = 2^20 relative Frobenius error {rel:.2e}")
 
 
-@pytest.mark.parametrize("K", [64, 1024])    # 1024: the K split, whose halves add with atomics
+@pytest.mark.parametrize("K", [64, 1024])    # a small product's kernel; test_gpu_gemm_routes takes the others
 def test_gemm_very_wide_row_stride(K):
     M, N = 8, 40
     ldc = (1 << 20) + 64
