@@ -19,9 +19,11 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     # up to 2^20 outputs: waves share K
     (1, 1, 32), (16, 16, 128), (17, 15, 160), (33, 47, 288), (65, 129, 1056), (16, 4000, 96), (33, 4097, 96),
-    (130, 2050, 64), (5000, 1, 32), (4097, 17, 160), (9, 40, 9248), (1024, 1024, 512),
-    # at the limit but without room for C in the workspace, and past the limit: 128 x 128 tiles, K whole
-    (1024, 1024, 64), (1025, 1024, 96), (300, 4000, 480),
+    (5000, 1, 32), (4097, 17, 160), (9, 40, 9248), (1024, 1024, 512),
+    # the same, tiles of 16 x 32, 32 x 64 and 64 x 32 outputs, several groups of K blocks for each wave
+    (7, 6161, 1184), (16, 11009, 1056), (31, 12301, 2080), (500, 2000, 2080),
+    # no room for C in the workspace, and past the limit: 128 x 128 tiles, K whole
+    (130, 2050, 64), (1024, 1024, 64), (1025, 1024, 96), (300, 4000, 480),
     # 128 x 128 tiles, K in two halves (of 8 and 8, 9 and 8, 17 and 16 blocks)
     (1025, 1024, 512), (300, 4000, 544), (1100, 1000, 1056),
     # 256 x 256 tiles, K whole and split
