@@ -87,10 +87,9 @@ def test_output_row_stride():
 @pytest.mark.parametrize("fmt", ["E4C3", "E3C3"])
 @pytest.mark.parametrize("M,K", [(9216, 8192), (8100, 4160)])
 def test_large_tensor_two_rounds(fmt, M, K):
-    """A reconstruction large enough for the launch's two chunks per thread (more chunks than 8192
-    workgroups of 256 threads can take in one round; 8100 x 4160 leaves the last threads one chunk),
-    as codes and scales the oracle quantizes from the seeded source: sampled rows, every 8-code
-    chunk of them, bit for bit."""
+    """Large reconstructions: from 2^24 quads of codes on each lane takes eight quads (9216 x 8192: whole
+    workgroups), below two (8100 x 4160), as codes and scales the oracle quantizes from the seeded source:
+    sampled rows, every code of them, bit for bit."""
     rng = np.random.default_rng(77)
     rows = np.unique(np.concatenate([np.arange(0, M, 127), [M - 1]]))
     codes = np.zeros((M, K), dtype=np.uint8)
@@ -109,3 +108,28 @@ def test_large_tensor_two_rounds(fmt, M, K):
     got = out[torch.from_numpy(rows).to(DEV)].cpu().numpy()
     exp = oracle.dequantize(oc, osc, f)
     assert np.array_equal(got.view(np.uint32), exp.view(np.uint32)), "sampled rows differ"
+
+
+@pytest.mark.parametrize("fmt", ["E4C3", "E3C3"])
+@pytest.mark.parametrize("pad", [0, 36])
+def test_eight_quads_with_a_partial_workgroup(fmt, pad):
+    """8195 x 8224: more than 2^24 quads and not a multiple of the 2048 that a workgroup takes, dense and into
+    the columns of a wider buffer.  Every row against one pattern of rows, repeated; the gaps stay as they were."""
+    M, K, P = 8195, 8224, 61
+    assert M * K // 4 >= 1 << 24 and M * K // 4 % 2048
+    rng = np.random.default_rng(78)
+    X = (rng.standard_normal((P, K)) * np.exp2(rng.uniform(-6, 6, (P, 1)))).astype(np.float32)
+    X[7, :32] = np.nan
+    X[8, 32:64] = 2.0 ** -140            # a scale at which levels are subnormal
+    oc, osc = oracle_quantize(X, fmt, 1)
+    exp = torch.from_numpy(oracle.dequantize(oc, osc, oracle.get_format(fmt)).view(np.int32)).to(DEV)
+    rows = torch.arange(M, device=DEV) % P
+    c = torch.from_numpy(np.ascontiguousarray(layout_codes(oc, fmt))).to(DEV)[rows].contiguous()
+    s = torch.from_numpy(osc).to(DEV)[rows].contiguous()
+    say(f"[dequantize] eight quads fmt={fmt} pad={pad}")
+    dst = torch.full((M, K + pad), 3.0, device=DEV)
+    cf.curvefp_dequantize(c, s, fmt, M, K, dst=dst[:, :K])
+    torch.cuda.synchronize()
+    bad = (dst[:, :K].contiguous().view(torch.int32) != exp[rows]).sum(dim=1)
+    assert int(bad.sum()) == 0, f"rows {torch.nonzero(bad)[:8, 0].tolist()} differ"
+    assert pad == 0 or bool((dst[:, K:] == 3.0).all()), "gaps written"
