@@ -150,9 +150,9 @@ int curvefp_quantize_mse(const void* src, int dtype, int64_t rows, int64_t cols,
  * scales [outer] (outer = rows for block_axis = 1, cols for 0), all equal, so every consumer
  * takes the operand as rowwise-scaled (block = the blocked extent).  A NaN or infinity
  * anywhere poisons the tensor (scale -128, zero codes).
- *   workspace  one 32-bit word of device memory (4-byte aligned), scratch of the call:
- *              calls that share it must be ordered.  (The partial maxima are kept in the code
- *              buffer until the codes overwrite them.)
+ *   workspace  one 32-bit word of device memory (required, 4-byte aligned), neither read nor
+ *              written: the partial maxima pass through the code buffer, which holds them until
+ *              the codes overwrite them.
  * The blocked extent must be a multiple of 32 and at most 2^30 (CURVEFP_ERR_SHAPE).  The source
  * is read twice (its maximum, then the codes).
  */

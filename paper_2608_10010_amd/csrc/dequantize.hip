@@ -31,7 +31,9 @@ namespace {
 // the first is written.  A level's bits at a scale that keeps it a normal number are its bits at scale 0 plus
 // the scale in the exponent field: one table lookup and one add; other scales take value_bits.
 // HBM-bound: 4000 x 11008 E4C3 51.0 -> 33.1 us (220 MB, 6.7 TB/s: the largest cache takes part), 32768 x 8192
-// 275 -> 234 us (5.8 TB/s), 2048 x 4096 E3C3 13.0 -> 8.2 us, 16 x 4096 3.2 -> 2.7 us.
+// 275 -> 234 us (5.8 TB/s), 2048 x 4096 E3C3 13.0 -> 8.2 us, 16 x 4096 3.2 -> 2.7 us.  What reads the result next does
+// not pay for the streaming stores: fp32 to E5C2 codes, back, and the result to bf16, 4000 x 11008 144.8 -> 138.0 us
+// (140.7 with these stores plain), 8192 x 4096 109.5 -> 106.7, 4096 x 14336 196.9 -> 182.5 (195.1).
 template <class F, int U>
 __global__ __launch_bounds__(256) void dequantize_kernel(const uint8_t* __restrict__ codes,
                                                          const int8_t* __restrict__ scales, uint64_t nquads,

@@ -943,7 +943,8 @@ __device__ __forceinline__ void requant_tile(f32x16 (&acc)[TM][4], const int* sA
 // them, in the order of either arrival (the sum is the same), and quantizes.  A wave takes 8 rows of a tile:
 // its 256 columns are 8 slot chunks of 1 KB (8 rows x 32 columns, coalesced) per half, all requested
 // before the first is used; they go through its own 8 KB of LDS, after which each lane holds one group of 32.
-// Bound by the slots' bytes (8 per output; 4.4 TB/s with the codes).  In the GEMM's epilogue the quantization
+// Bound by the slots' bytes (8 per output; 4.4 TB/s with the codes); two workgroups share a unit, one where the output
+// is E5C2 (its table of 17 KB beside 64 KB of slices).  In the GEMM's epilogue the quantization
 // ran in one wave per SIMD and, as only the half that arrives second has the sum, in half of the
 // workgroups; 2048 x 4096 x 4096 E3C3, GEMM and requantization: 203 -> 171 + 17 us, 2048 x 2048 x 8192 the
 // whole call 275 -> 213, 2048 x 4096 x 1024 87 -> 74 us.
@@ -1456,8 +1457,8 @@ hipError_t small_from_planes(const SmallPlan& p, const char* pa, const int* maxA
 // and takes about 0.6 of the time (4096 K: 95 against 161 us with every unit busy, 65 against 107 us with
 // a quarter of them), so it pays where the larger tiles leave more of their rounds empty: 512 x 4096
 // x 4096 66 against 107 us, 1300 x 6144 x 2048 (3 rounds against 2) 131 against 153 us, but
-// 1500 x 4096 x 4096 (2 against 1) 160 against 143 us.  From 256 large tiles on K is not split and the
-// larger tiles always win.
+// 1500 x 4096 x 4096 (2 against 1) 160 against 143 us.  K whole (below 512): 512 x 4096 x 256 12.0 against 20.4 us, 2048 x
+// 4096 x 480 30.2 against 36.4.  From 256 large tiles on K is not split and the larger tiles always win.
 bool mid_tiles(int64_t M, int64_t N, int64_t K) {
     const WsLayout w = ws_layout(M, N, K);
     const int64_t large = w.rta * w.rtb * w.splits, small = ((M + 127) / 128) * ((N + 127) / 128);

@@ -10,9 +10,10 @@
 // second slice's fragments are read under the first slice's MFMAs; then, after the barrier, block s + 2 is
 // copied into the stage just freed and block s + 1's first slice is read under the second slice's MFMAs.
 //
-// What bounds it: alone on a compute unit the matrix pipe is about half busy (24 MFMAs of 32 cycles per
-// wave and step, 0.9 us a step for two waves per SIMD), the rest is the barrier and the fragment reads,
-// which a quarter-size tile has twice as many of per MFMA; with the chip full it is the power limit.
+// What bounds it: on a compute unit with a workgroup the matrix pipe is 72% busy (333 x 6144 x 4096, the whole
+// kernel; the LDS half of the time), the rest is the barrier and the fragment reads, which a quarter-size tile has
+// twice as many of per MFMA; there 144 workgroups on 256 units leave the others idle.  With the chip full it is the
+// power limit.
 // Measured, E4C3, operands prepared, 256 x 256 kernel -> this one: 512 x 4096 x 4096 107 -> 66 us,
 // 1024 x 4096 x 1024 50 -> 31 us, 1000 x 2500 x 2080 85 -> 41 us.  Variants on 1024 x 4096 x 4096 (95 us):
 // the halves in two workgroups with partial sums through memory 98 us (and 5 us to clear the counters);

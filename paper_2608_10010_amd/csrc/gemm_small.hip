@@ -16,7 +16,9 @@
 // and the order of the sum depends on (M, N, K) alone, so every entry point returns the same C.
 //
 // What bounds it: from codes the expansion (per 8 codes about 30 vector instructions and 8 LDS gathers, of
-// both operands in every tile), from planes the caches that deliver them.  Measured, weights from HBM,
+// both operands in every tile: 16 x 4096 x 4096 issues a vector instruction in 56% of a busy unit's slots, its waves
+// wait for the rest, and filling the table and the first loads take half of the 12 us), from planes the memory:
+// 32 x 14336 x 4096 reads 239 MB of them in 35 us (6.9 TB/s).  Measured, weights from HBM,
 // 256 x 256 kernel with its preparation -> this one: 16 x 4096 x 4096 E3C3 codes 123 -> 14 us (from planes
 // 106 -> 12 us), 32 x 14336 x 4096 E4C3 181 -> 36 us (119 -> 40 us), 128 x 128 x 128 27 -> 6 us.
 #include "curvefp_internal.hpp"
@@ -550,8 +552,8 @@ hipError_t launch_planes(const SmallPlan& p, const SmallOperand& A, const SmallO
 // either operand), where curvefp_gemm_requant keeps it.
 // The tile is the largest that still makes 192 workgroups for the 256 compute units (each operand row is
 // expanded once per tile that needs it), without going past twice the operand's rows.  Eight waves share K
-// where a unit has one workgroup, four where it has several (128 x 4096 x 4096, 256 workgroups: 33.8 us
-// with eight, 38.2 with four; 333 x 6144 x 4096, 1152: 151 and 126 us).
+// where a unit has one workgroup, four where it has several (E4C3 codes, 128 x 4096 x 4096, 256 workgroups: 32.7 us
+// with eight, 37.2 with four; 250 x 4096 x 4096, 512: 62.3 and 53.0 us).
 bool small_plan(int64_t M, int64_t N, int64_t K, SmallPlan* p) {
     constexpr int64_t MOST = (int64_t)1 << 20;
     if (M > MOST || N > MOST || M * N > MOST) return false;

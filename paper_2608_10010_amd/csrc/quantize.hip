@@ -34,8 +34,8 @@ __constant__ uint32_t g_qlut[NUM_FORMATS][QLUT_MAX] = CURVEFP_QLUT_INIT;
 // decision point is never passed and the rank is the bucket's base rank alone (one byte)
 __constant__ __attribute__((aligned(16))) uint8_t g_qlut8[NUM_FORMATS][QLUT_MAX] = CURVEFP_QLUT8_INIT;
 __constant__ uint32_t g_lmax_mant[NUM_FORMATS] = CURVEFP_LMAX_MANT_INIT;
-// reconstruction tables for the static-scale search (the dequantizer's, see codec.hpp): binary
-// radix 8 entries by curve index, rational radix 128 by magnitude rank
+// the dequantizer's tables (see codec.hpp), for quantize-and-prepare with a reconstruction: binary radix 8 entries by
+// curve index, rational radix 128 by magnitude rank
 __constant__ uint32_t g_qr_mant[NUM_FORMATS][128] = CURVEFP_QR_MANT_INIT;
 __constant__ uint64_t g_qr_sig[NUM_FORMATS][128] = CURVEFP_QR_SIG_INIT;
 // the GEMM operands' expansion pairs (the GEMM's table, gemm.hip), for quantize-and-prepare
@@ -539,20 +539,20 @@ hipError_t launch_cols_tile(const void* src, int64_t rows, int64_t cols, int64_t
 // is then the shortest: a tile's own time counts, and 128 columns leave units idle.  Beyond that, bf16 sources to
 // 8-bit codes take eight values at a time, in tiles of 128 columns (the table is filled half as often) or, where the
 // scale pass has written the scales, of 64.  bf16, 32 at once x 64 / eight x 64 / eight x 128: 512 x 4096 E4C3 4.5 /
-// 4.6 / 5.2 us, 1536 x 4096 (768 tiles) 7.0 / 7.1 / 7.9, 1792 x 4096 9.6 / 8.3 / 8.0, 4096 x 4096 17.0 / 14.9 / 14.5, 8192 x
-// 14336 E5C2 109 / 98 / 82; with given scales (G = 64) 1536 x 4096 8.5 / 8.7 / 10.6, 2048 x 4096 11.2 / 10.2 / 11.6,
+// 4.6 / 5.2 us, 1536 x 4096 (768 tiles) 7.0 / 7.1 / 7.9, 1792 x 4096 9.6 / 8.3 / 8.0, 4096 x 4096 17.0 / 14.9 / 14.5,
+// 8192 x 14336 E5C2 109 / 98 / 82; with given scales (G = 64) 1536 x 4096 8.5 / 8.7 / 10.6, 2048 x 4096 11.2 / 10.2 / 11.6,
 // 8192 x 14336 E4C3 125 / 117 / 123.  For fp32 sources (the tile in LDS holds them to 3 waves per SIMD) and 7-bit
 // codes eight at a time measured 1-3% slower at every size.
 template <class F>
 hipError_t launch_cols_tiled(const void* src, int dtype, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                              int8_t* scales, int fidx, int given, int64_t nsb, Div32 dgq, hipStream_t s) {
-    if (dtype != 1) return launch_cols_tile<F, false, 64, false>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    auto launch = [&](auto tile) { return tile(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s); };
+    if (dtype != 1) return launch(launch_cols_tile<F, false, 64, false>);
     if constexpr (!F::PACKED7) {
         if ((cols + 63) / 64 * (rows / TT_ROWS) > 768)
-            return given ? launch_cols_tile<F, true, 64, true>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s)
-                         : launch_cols_tile<F, true, 128, true>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+            return given ? launch(launch_cols_tile<F, true, 64, true>) : launch(launch_cols_tile<F, true, 128, true>);
     }
-    return launch_cols_tile<F, true, 64, false>(src, rows, cols, ld, codes, scales, fidx, given, nsb, dgq, s);
+    return launch(launch_cols_tile<F, true, 64, false>);
 }
 
 // given != 0: the block scales (blocks of `block` rows) are already in `scales`
@@ -720,8 +720,10 @@ __global__ __launch_bounds__(256) void quantize_compact_kernel(const void* __res
 
 // Rows that fit in registers (U chunks of 8 per lane, WPR waves per row) with blocks of 32..512 (a power of
 // two): the source is read once, a block's maximum is taken over its lanes, the row's reference over its
-// waves.  HBM-bound; the general kernel above reads a row twice and holds 36 KB of LDS per row, so that
-// three rows share a compute unit (2048 x 4096 bf16 to E3C3, G64: 12.8 us, 10.2 here; 8192 x 1024 32 and 11.6 us, 8192 x 14336 125 and 92 us).
+// waves.  Bound by vector instructions (75% of a busy unit's slots on 2048 x 4096 bf16 to E3C3) and by the start and
+// end of a short launch; the general kernel above reads a row twice and holds 36 KB of LDS per row beside its table,
+// so that two to four rows share a unit.  bf16 to E3C3, G64, general kernel and this one: 2048 x 4096 12.0 and 9.5 us,
+// 8192 x 1024 31.5 and 11.4, 8192 x 14336 122 and 83.
 template <class F, bool BF16, int U, int WPR>
 __global__ __launch_bounds__(256) void quantize_compact_rows_kernel(const void* __restrict__ src, int64_t rows,
                                                                     uint32_t cpr, int64_t ld, int lgl, int S,
@@ -980,7 +982,8 @@ hipError_t launch_compact_type(const void* src, int64_t rows, int64_t cols, int6
     // a wave per row of up to 1024, a workgroup per row of up to 16384, two to eight chunks per lane (fewer
     // lanes with more chunks each hide less of the loads: a wave per row of 4096 took 13.5 us where the
     // workgroup takes 10.2, and the general kernel 12.8; eight chunks per lane for rows of 8704 to 12288, where up to
-    // half of them are past the end, 3-5% more than six: 4096 x 11264 E3C3, G32: 40.6 and 38.4 us, the general kernel 47.1)
+    // half of them are past the end, 3-5% more than six: 4096 x 11264 E3C3, G32: 40.6 and 38.4 us, the general kernel
+    // 47.1)
     if (block <= 512 && (block & (block - 1)) == 0 && cols <= 16384) {
         int lgl = 0;
         while ((8 << lgl) < block) lgl++;

@@ -12,13 +12,15 @@
 // candidate out before it is evaluated (sums of non-negative terms never fall, rounded or not).  Of normally
 // distributed weights four blocks in five stop there.  The (block, candidate) pairs left are collected in LDS
 // and shared out over the workgroup's threads, so that a wave evaluates 64 of them and not the few of its own
-// blocks; the blocks whose scale moved are written again in the same way.  A scale above the ceil-absmax scale clips
-// nothing, so nothing rules it out: every thread evaluates those of its own block, before the others, from the
-// registers that hold it (from the list, E4C3 with radix 2^(3/4), fp32, blocks of 32 took 527 us for 8192 x 8192 and one
-// candidate, 331 from the registers).
+// blocks; the blocks whose scale moved are written again in the same way.  A scale above the ceil-absmax scale
+// clips nothing, so nothing rules it out: every thread evaluates those of its own block, before the others, from
+// the registers that hold it (E4C3 with radix 2^(3/4), fp32, 8192 x 8192, blocks of 32, one candidate: 527 us from
+// the list, 331 from the registers).
 //
-// What bounds it: vector instructions (about 25 per element and candidate evaluated).  4096 x 4096 bf16 to
-// E3C3, four candidates, blocks of 32 / 64 / 512: 132 / 142 / 748 -> 46 / 50 / 155 us.
+// What bounds it: waiting.  4096 x 4096 bf16 to E3C3, blocks of 64: vector instructions (about 32 per element, 83% of
+// the lanes active) take 28% of a busy unit's slots and LDS 11%; the two waves of a SIMD wait 70% of their time, for the
+// serial fp64 sum of a block, its table lookups, and at the barriers of share_out, where one wave works on the few
+// blocks listed.  Four candidates, blocks of 32 / 64 / 512: 132 / 142 / 748 -> 46 / 50 / 155 us.
 #include "codec.hpp"
 #include "curvefp_internal.hpp"
 #include "device_util.hpp"
