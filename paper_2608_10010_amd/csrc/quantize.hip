@@ -337,9 +337,10 @@ __global__ __launch_bounds__(256) void block_scales_cols_kernel(const void* __re
 }
 
 // NT: streaming loads.  Each workgroup fills the table first, so fp32 sources (their table is two to four times
-// bfloat16's) run in workgroups of about two rounds, at least 4096 and at most 32768 of them, and take plain loads.  One
-// round each / 4096 at every size / this rule, E4C3: 4000 x 11008 46.0 / 38.4 / 38.4 us, 8192 x 14336 120 / 111 / 103,
-// 32768 x 8192 227 / 255 / 228, 32768 x 14336 (E3C3) 433 / 480 / 426.  bfloat16: up to 32768 (4096 measured 2-9%
+// bfloat16's) take plain loads and 4096 workgroups of up to four rounds, and beyond that, where 4096 fall behind the memory,
+// workgroups of two rounds, at most 32768.  One round each / 4096 at every size / two rounds, E4C3: 4000 x 11008 46.0 /
+// 38.0 / 38.4 us (E5C2 54.7 / 40.4 / 41.2), 8192 x 8192 64 / 55.2 / 53.7 (E5C2 80 / 57.3 / 57.9), 8192 x 14336 120 / 111 /
+// 103, 32768 x 8192 227 / 255 / 228, 32768 x 14336 (E3C3) 433 / 480 / 426.  bfloat16: up to 32768 (4096 measured 2-9%
 // faster on E5C2, 4% slower on 32768 x 8192 and on E3C3).
 template <class F, bool BF16, int U, bool NT = BF16>
 hipError_t launch_rows_u(const void* src, int64_t rows, int64_t cols, int64_t ld, int fidx, uint8_t* codes,
@@ -351,7 +352,7 @@ hipError_t launch_rows_u(const void* src, int64_t rows, int64_t cols, int64_t ld
         const int64_t nr = rows - r0 < slab ? rows - r0 : slab;
         const int64_t nchunks = nr * cpr;
         int64_t blocks = (nchunks + 256 * U - 1) / (256 * U);
-        if (!BF16 && blocks > 4096) blocks = blocks > 8192 ? (blocks + 1) / 2 : 4096;
+        if (!BF16 && blocks > 4096) blocks = blocks > 16384 ? (blocks + 1) / 2 : 4096;
         blocks = blocks < 32768 ? blocks : 32768;
         const void* sp = reinterpret_cast<const char*>(src) + r0 * ld * (BF16 ? 2 : 4);
         uint8_t* cp = codes + (F::PACKED7 ? r0 * (cols / 32) * 28 : r0 * cols);

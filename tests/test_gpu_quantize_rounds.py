@@ -1,4 +1,4 @@
-"""curvefp_quantize of fp32 rows whose workgroups take several rounds: both sides of the counts (4096 and 8192
+"""curvefp_quantize of fp32 rows whose workgroups take several rounds: both sides of the counts (4096 and 16384
 rounds of 512 chunks) where the number of workgroups changes, a last round that is not full, a row stride.  Codes and
 scales equal to those of the same rows quantized a few at a time, which are one round each."""
 
@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fmt", ["E4C3", "E5C2", "E3C3", "E4C3_r3/4"])
-@pytest.mark.parametrize("rows,cols,pad", [(4096, 4096, 0), (4097, 4096, 0), (8192, 4096, 0), (8193, 4096, 8),
-                                           (10001, 4128, 0)])
+@pytest.mark.parametrize("rows,cols,pad", [(4096, 4096, 0), (4097, 4096, 0), (16384, 4096, 0), (16385, 4096, 8),
+                                           (10001, 4128, 0), (20001, 4128, 0)])
 def test_rounds(fmt, rows, cols, pad):
     say(f"[quantize rounds] {fmt} {rows} x {cols} + {pad}")
     g = torch.Generator(device=DEV).manual_seed(rows)
