@@ -39,3 +39,23 @@ def test_split_requant(ofmt, M, N, K, G, poison):
     assert a.numel() == b.numel() and bool((a == b).all()), f"{int((a != b).sum())} code bytes differ"
     if poison:
         assert bool((scales[M - 1] == -128).all()) and bool((scales[:, -1] == -128).all())
+
+
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("M,N,K,G", [(1500, 3840, 544, 64), (2049, 4128, 96, 32), (2049, 4224, 64, 128)])
+def test_input_formats(fmt, M, N, K, G):
+    """Every input format (the requantizing 256 x 256 kernel is compiled for each one's exponent offset), K in halves
+    and whole, where the tile is quantized in the epilogue: every output format."""
+    rng = np.random.default_rng(M + G)
+    A = (rng.standard_normal((M, K)) * np.exp2(rng.uniform(-4, 4, (M, 1)))).astype(np.float32)
+    B = (rng.standard_normal((N, K)) * 0.05).astype(np.float32)
+    ca, sa = cf.curvefp_quantize(to_dev(A, "f32"), fmt)
+    cb, sb = cf.curvefp_quantize(to_dev(B, "f32"), fmt)
+    ws = cf.gemm_workspace(M, N, K, DEV)
+    C = cf.curvefp_gemm_ws(ca, sa, cb, sb, M, N, K, fmt)
+    for ofmt in FMTS:
+        say(f"[requant slots] {fmt} -> {ofmt} M={M} N={N} K={K} G={G}")
+        codes, scales = cf.curvefp_gemm_requant(ca, sa, cb, sb, M, N, K, fmt, ofmt, workspace=ws, out_block=G)
+        c2, s2 = cf.curvefp_quantize(C, ofmt, block=G)
+        torch.cuda.synchronize()
+        assert torch.equal(scales, s2) and torch.equal(codes.reshape(-1), c2.reshape(-1)), f"{fmt} -> {ofmt}"
