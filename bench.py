@@ -28,8 +28,8 @@ Also reported, each in a key of its own:
                    them (E5C2 output gradients times the reused E4C3 forward codes);
   radix_variants, static_scales, requant, block_sizes
                    the inference workload in the E4C3 radix variants, with
-                   reconstruction-error scale search, with its output requantized in
-                   the epilogue, and with one scale per 32, 64, 512 or K elements;
+                   reconstruction-error scale search, with its output requantized, and
+                   with one scale per 32, 64, 512 or K elements;
   cpu_baseline     the CPU oracle on a bounded row sample of the headline workload,
                    with the host's CPU model, affinity and thread count.
 --cpu-baseline-table times the oracle on every configuration instead (full size
@@ -74,7 +74,7 @@ def parse():
     p.add_argument("--no-backward", action="store_true",
                    help="skip the mixed-format backward GEMMs (E5C2 gradients x reused E4C3 codes)")
     p.add_argument("--no-requant", action="store_true",
-                   help="skip the GEMM with output requantization (fused epilogue vs GEMM + quantize)")
+                   help="skip the GEMM with output requantization (one call vs GEMM + quantize)")
     p.add_argument("--no-blocks", action="store_true",
                    help="skip the block-size sweep (G = 32, 64, 512, K) of the inference workload")
     p.add_argument("--no-static", action="store_true",
@@ -930,7 +930,7 @@ def backward_mixed(cf, W, dev, stream, reps: int = 20):
 
 def requant(cf, w, ca, sa, cb, sb, dev, stream, reps: int = 20):
     """The inference GEMM with its output requantized to E3C3 (the next layer's activation
-    format): curvefp_gemm_requant (fused epilogue) against curvefp_gemm_ws followed by
+    format): curvefp_gemm_requant ("fused") against curvefp_gemm_ws followed by
     curvefp_quantize of the fp32 C; median of `reps` individually timed calls each."""
     import numpy as np
     import torch

@@ -687,7 +687,7 @@ def curvefp_gemm_requant(a_codes: torch.Tensor, a_scales: torch.Tensor, b_codes:
                          out_codes: Optional[torch.Tensor] = None, out_scales: Optional[torch.Tensor] = None,
                          workspace: Optional[torch.Tensor] = None, stream=None,
                          out_block: int = 32) -> Tuple[torch.Tensor, torch.Tensor]:
-    """curvefp_gemm_ws's product requantized in the epilogue: codes/scales of C in out_fmt,
+    """curvefp_gemm_ws's product requantized on the device: codes/scales of C in out_fmt,
     blocks of out_block (32, 64, 128 or 256) along each row (equal to curvefp_quantize of the
     fp32 C with that block)."""
     what = "curvefp_gemm_requant"

@@ -32,8 +32,8 @@ def prepared_product(qa, fa, qb, fb, M, N, K, c=None, block=32):
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("shape", [(200, 136, 96), (1, 1, 32), (129, 257, 320), (64, 300, 1024), (300, 520, 640)])
 def test_shapes(fmt, shape):
-    """Ragged edges, a single element, and K split in two (fewer than 256 output tiles with
-    K >= 512: the GEMM's workspace holds the partial sums)."""
+    """Ragged edges, a single element, long K: small products (test_gpu_gemm_tiles and test_gpu_gemm_routes take
+    the larger tiles, K in halves among them)."""
     M, N, K = shape
     rng = np.random.default_rng(M * 7 + N + 5 * K)
     A = (rng.standard_normal((M, K)) * np.exp2(rng.uniform(-6, 6, (M, 1)))).astype(np.float32)
@@ -127,8 +127,8 @@ def test_prepared_weights_serve_many_products():
 
 
 def test_row_stride_and_reused_workspace():
-    """An output with a row stride (columns past N untouched), and one workspace for a split-K
-    product then a smaller one."""
+    """An output with a row stride (columns past N untouched), and one workspace for a product then a smaller one
+    (small products; test_gpu_gemm_routes leaves other things in the workspaces of the larger tiles)."""
     rng = np.random.default_rng(71)
     ws = torch.empty(cf.curvefp_gemm_prepared_workspace_bytes(300, 260, 2048), dtype=torch.uint8, device=DEV)
     for (M, N, K) in ((300, 260, 2048), (40, 72, 1024)):

@@ -1,5 +1,4 @@
-"""GPU parity of curvefp_gemm_requant: curvefp_gemm_ws's product requantized in the GEMM's
-epilogue.  The contract is exact: the codes and scales equal curvefp_quantize (blocks of 32 along
+"""GPU parity of curvefp_gemm_requant: curvefp_gemm_ws's product requantized on the device.  The contract is exact: the codes and scales equal curvefp_quantize (blocks of 32 along
 the rows) of the fp32 C that curvefp_gemm_ws returns, bit for bit.  Against the oracle, the codes
 of the exact sum (rounded to fp32 and quantized by the oracle) agree except where the fp32 C and
 the exact value fall on opposite sides of a decision point, which moves a code by one level."""
@@ -48,7 +47,8 @@ def sources(M, N, K, seed):
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("ofmt", FMTS)
 def test_equals_quantized_gemm_ws(fmt, ofmt):
-    """Every input format x output format; ragged M, N a multiple of 32 but not of 256, K split."""
+    """Every input format x output format; ragged M, N a multiple of 32 but not of 256 (a small
+    product; test_gpu_gemm_requant_slots takes the large tiles)."""
     M, N, K = 300, 544, 640
     A, B = sources(M, N, K, 3 * FMTS.index(fmt) + FMTS.index(ofmt))
     say(f"[gemm_requant] {fmt} -> {ofmt} M={M} N={N} K={K}")
@@ -59,7 +59,7 @@ def test_equals_quantized_gemm_ws(fmt, ofmt):
 
 @pytest.mark.parametrize("shape", [(4096, 4096, 128), (256, 288, 32), (40, 32, 96)])
 def test_shapes(shape):
-    """No K split (256 tiles), a single K block, a single partial tile."""
+    """256 tiles with K whole (quantized in the epilogue), a single K block, a single partial tile."""
     M, N, K = shape
     A, B = sources(M, N, K, M + N + K)
     say(f"[gemm_requant] shape {shape}")
@@ -128,7 +128,7 @@ def test_inference_full_size(ofmt):
 def test_output_blocks_of_g(ofmt, G, shape):
     """Output blocks of 64, 128 and 256 (the next layer's activations at the paper's G64): equal
     to curvefp_quantize of curvefp_gemm_ws's fp32 C with that block, bit for bit; ragged M, N a
-    multiple of G but not of 256, K split and not, and the full inference shape."""
+    multiple of G but not of 256 (small products), the full inference shape (K in halves) and 256 tiles with K whole."""
     M, N, K = shape
     fmt = "E3C3"
     A, B = sources(M, N, K, G + FMTS.index(ofmt))

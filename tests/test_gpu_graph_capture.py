@@ -23,7 +23,7 @@ def same(x: torch.Tensor, y: torch.Tensor, what: str):
 
 @pytest.mark.parametrize("fmt", ["E4C3", "E3C3"])
 def test_captured_step_replays(fmt):
-    M, N, K = 520, 300, 1024            # fewer than 256 tiles and K >= 512: the GEMM splits K
+    M, N, K = 520, 300, 1024            # a small product; test_gpu_gemm_routes captures the larger tiles
     gen = torch.Generator(device=DEV)
     x = torch.empty((M, K), dtype=torch.bfloat16, device=DEV)
     wt = torch.empty((N, K), dtype=torch.bfloat16, device=DEV)

@@ -4,7 +4,8 @@ Such a value poisons its block (scale -128, zero codes), which reconstructs to N
 GEMM computes deq(A) deq(B)^T in IEEE terms: every output in a row of A or of B that holds a
 poisoned block is NaN (zero partners included), every other output is the usual product.
 Checked against the oracle (NaN at exactly its places, the element-wise bound elsewhere) for the
-fused, workspace, mixed-format and requantizing entry points, with and without the K split."""
+fused, workspace, mixed-format and requantizing entry points on small products (test_gpu_gemm_tiles and
+test_gpu_gemm_requant_slots hold poisoned rows and columns to the same on the larger tiles)."""
 
 import numpy as np
 import pytest
@@ -33,7 +34,7 @@ def sources(M, N, K, seed):
 
 
 @pytest.mark.parametrize("fmt", BINARY_FMTS + ("E4C3_r3/4",))
-@pytest.mark.parametrize("K", [256, 1024])      # 1024: few tiles and 32 blocks, so K is split
+@pytest.mark.parametrize("K", [256, 1024])      # one or several groups of K blocks for each wave
 def test_fused_and_workspace(fmt, K):
     M, N = 200, 136
     A, B = sources(M, N, K, 61 + K)

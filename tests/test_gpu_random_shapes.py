@@ -1,8 +1,8 @@
 """Seeded random shapes through every single-format GEMM entry point: for each case (M, N, K, format,
 block size drawn from one generator), curvefp_gemm, curvefp_gemm_ws and prepare + gemm_prepared give
 the same C bit for bit, and sampled rows agree with the exact phase-binned oracle within the GEMM
-parity bound.  Shapes span single partial tiles, ragged edges, K split in two and several rounds of
-tiles; block sizes 32, 64, 128 and rowwise."""
+parity bound.  Shapes span single partial tiles, ragged edges and K from one block to 64, most of them small
+products; block sizes 32, 64, 128 and rowwise."""
 
 import numpy as np
 import pytest
