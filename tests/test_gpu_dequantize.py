@@ -110,7 +110,7 @@ def test_large_tensor_two_rounds(fmt, M, K):
     assert np.array_equal(got.view(np.uint32), exp.view(np.uint32)), "sampled rows differ"
 
 
-@pytest.mark.parametrize("fmt", ["E4C3", "E3C3"])
+@pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("pad", [0, 36])
 def test_eight_quads_with_a_partial_workgroup(fmt, pad):
     """8195 x 8224: more than 2^24 quads and not a multiple of the 2048 that a workgroup takes, dense and into
