@@ -1,5 +1,5 @@
 """curvefp_quantize of fp32 rows whose workgroups take several rounds: both sides of the counts (4096 and 16384
-rounds of 512 chunks) where the number of workgroups changes, a last round that is not full, a row stride.  Codes and
+rounds of 512 chunks) where the number of workgroups changes, a last one that is not full, a row stride.  Codes and
 scales equal to those of the same rows quantized a few at a time, which are one round each."""
 
 import pytest
